@@ -28,17 +28,43 @@
 //       of dZ sum to zero, so log R stands in for the logits);  at t = 1
 //       d alpha_R is added to dQ (alpha_R = the rows of Q) and c_R is constant.
 //
-// Every unit keeps its matrices in LDS tiles, fp32 except the whole-unit tiles
-// that are exact in a 16-bit element type at 64 and 128 rows (see Geo), and
-// runs every product on v_mfma_f32_16x16x4f32.  A unit sizes its tiles by its
-// own dimension (m for l_bwd, b for r_bwd).  When its tiles do not fit at
-// once, it walks its own rows (j in r_bwd, l in l_bwd) in chunks, the sums
-// over those rows (dK, dV, dY, d alpha_L, d c_L) accumulating in registers.  The gradients of the states and the dQ, dK
-// accumulators are fp32 in the workspace.  Within a launch the units write
-// disjoint rows, and launches that touch the same rows are ordered on the
-// stream, so read-modify-writes need no atomics and the result is
-// deterministic.  dq and dk are written in the element type by the step-1
-// R launch (the last one to touch them), dv by the step-T R launch.
+// Products.  The sweep's arithmetic is fp32: gradients, factors and
+// accumulators are fp32, and every operand keeps all its bits.  An fp32 value
+// is the exact sum of three bf16 values (its leading 8 bits, the next 8, the
+// rest: `split`), an fp16 value of two, a bf16 value of one; these are the
+// operand's planes.  A product runs on the bf16 matrix instruction (16x16x32:
+// 16 times the fp32 one's rate) once for every pair of planes p, q with
+// p + q <= 2, accumulating in fp32: 1 to 6 instructions a tile and chunk.  The
+// pairs left out are below 2^-26 of the product, less than the rounding of one
+// fp32 multiply.
+//
+// A unit (a block k of r_bwd, a class j of l_bwd) is one workgroup.  Its
+// columns (keys i, or key blocks k) are shared out over the waves in groups of
+// IPW 16-wide tiles, whose operands a wave holds in registers for the whole
+// unit; its rows (j, or l) pass through LDS in chunks of C.  Per chunk:
+//   1. the chunk's row operands go to LDS as planes (loaded a chunk ahead);
+//   2. wave (jt, ig) forms the transposed score tiles of row tile jt and its
+//      own columns, and the gradient of the factor, in the same registers
+//      (lane: columns 16t + 4g + q of row lane % 16);
+//   3. one exchange of partial row sums gives the softmax and its pull-back;
+//   4. the factor and the gradient of its logits go to LDS as planes, and the
+//      products that contract over the rows (into registers, for the whole
+//      unit) and over the columns (a tile of the row operand's gradient) follow.
+// A unit sizes its tiles by its own dimension (m for l_bwd, b for r_bwd).
+//
+// What bounds it: VALU issue and the latency of the phases between barriers.
+// At 16 heads of 128 x 128 blocks, d = 64, T = 2, bf16, the four launches take
+// r_bwd 201 and 126 us (t = 2, t = 1), l_bwd 147 and 168 us; on the fp32
+// matrix instruction, with the factors in LDS as fp32, they took 390, 347,
+// 289 and 345 us.  Their bytes alone (67 MB a state in fp32) take about 70 us
+// each.  VALU is active 40% of the time and the matrix cores 25%.
+//
+// The gradients of the states and the dQ, dK accumulators are fp32 in the
+// workspace.  Within a launch the units write disjoint rows, and launches that
+// touch the same rows are ordered on the stream, so read-modify-writes need no
+// atomics and the result is deterministic.  dq and dk are written in the
+// element type by the step-1 R launch (the last one to touch them), dv by the
+// step-T R launch.
 #pragma once
 
 #include "ma_kernels.hpp"
@@ -47,7 +73,7 @@ namespace ma {
 
 template <typename T> struct BwdBufs {
     const T *q, *k, *v, *dout;  // [B*H][n][d]
-    const T *aR, *aL, *Y;       // states of the step being undone ([m][b][D], [b][m][D], [b][m][D], D the tile width)
+    const T *aR, *aL, *Y;       // states of the step being undone ([m][b][d], [b][m][d], [b][m][d])
     const float *cR, *cL;       // c_R [b][m] (j-major), c_L [m][b] (k-major), as the forward writes them
     float *dQ, *dK;             // fp32 accumulators [B*H][n][d]
     T *dq, *dk, *dv;            // results [B*H][n][d]
@@ -75,279 +101,451 @@ __device__ inline int live_rows(const BwdDims &dm, int64_t bh)
     return len < 0 ? 0 : len > dm.n ? dm.n : len;
 }
 
-// Row strides (floats) of the LDS tiles: 16-byte rows, 68 floats for tiles
-// of up to 64 columns, 100 and 148 for 96 and 128.  The 64-column stride is
-// the smallest measured: at 16-row units the smaller tiles let six workgroups
-// share a CU instead of five (11% faster), and strides of 72 to 88 were no
-// faster at 64 or 128 rows.
-constexpr int row_stride(int cols) { return cols <= 64 ? 68 : cols <= 96 ? 100 : 148; }
+typedef float f32x2 __attribute__((ext_vector_type(2)));
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 
-constexpr int unit_waves(int S) { return S >= 64 ? 16 : S / 4; }
+// bf16 planes of an element type (split).
+template <typename T> constexpr int planes_of = std::is_same<T, float>::value ? 3 : std::is_same<T, __bf16>::value ? 1 : 2;
 
-// Whether two workgroups of a unit kernel share a CU: 64-row units at D = 64
-// with 16-bit elements, whose LDS (16-bit unit tiles) leaves room for two.
-// Their kernels carry a waves-per-SIMD bound that keeps the registers of two.
-constexpr bool two_per_cu(int S, int D, int elem_bytes) { return S == 64 && D == 64 && elem_bytes == 2; }
+// x[0..N) as the sum of NP bf16 planes, each the nearest bf16 value of what
+// the planes before it leave.
+template <int NP, int N, typename V> __device__ inline void split(const float *x, V (&p)[NP])
+{
+    float r[N];
+#pragma unroll
+    for (int i = 0; i < N; ++i) r[i] = x[i];
+#pragma unroll
+    for (int a = 0; a < NP; ++a) {
+#pragma unroll
+        for (int i = 0; i < N; i += 2) {  // two at a time: one conversion, and the halves of its result back as floats
+            const bf16x2 h = __builtin_convertvector((f32x2{r[i], r[i + 1]}), bf16x2);
+            p[a][i] = h[0];
+            p[a][i + 1] = h[1];
+            if (a + 1 < NP) {
+                uint32_t u;
+                __builtin_memcpy(&u, &h, 4);
+                r[i] -= __uint_as_float(u << 16);
+                r[i + 1] -= __uint_as_float(u & 0xffff0000u);
+            }
+        }
+    }
+}
 
-// With 16-bit elements (H16) the whole-unit tiles that are exact in the
-// element type (alpha_L in l_bwd, K and V in r_bwd) can be held as 16-bit
-// LDS tiles of row stride LD16, converted on every read (HALF):
-// - at 128 rows and D = 128, where two fp32 128 x 128 tiles alone would fill
-//   the LDS (the forward takes fp32 at D = 128 for blocks of up to 64 rows);
-// - at 64 rows and D = 64, where with rows in chunks of 32 it brings a unit under half
-//   the LDS, so that two workgroups share a CU and one's loads overlap the
-//   other's compute.
-template <int S, int D, bool H16 = false> struct Geo {
-    static constexpr bool HALF = H16 && (S == 128 ? D == 128 : S == 64 && D == 64);
-    static constexpr int BUDGET = (HALF && S == 64) ? 20480 : 40960;  // floats of LDS per workgroup
-    static constexpr int LD16 = D + 8;  // row stride (elements) of a 16-bit tile: 16-byte rows
-    static constexpr int W = unit_waves(S);
-    static constexpr int NTH = 64 * W;
-    static constexpr int LD = row_stride(D);
-    static constexpr int LS = row_stride(S);
-    // floats of the whole-unit tiles (the larger need, l_bwd's, when HALF)
-    static constexpr int UNIT = HALF ? S * LD16 / 2 + S * LD : 2 * S * LD;
-    static constexpr int lds_floats(int c) { return UNIT + 3 * c * LD + 2 * c * LS + 2 * S; }
-    static constexpr int C = lds_floats(S) <= BUDGET ? S : lds_floats(32) <= BUDGET ? 32 : 16;
-    static constexpr int NCH = S / C;
-    // row passes: a row of S scores spans SPAN lanes (CPL columns each), a wave
-    // instruction covers RPW rows
-    static constexpr int SPAN = S < 64 ? S : 64, RPW = 64 / SPAN, CPL = S > 64 ? S / 64 : 1;
-    static_assert(lds_floats(C) <= 40960, "tile shape exceeds the LDS of one CU");
+__device__ inline f32x4 mfma(bf16x8 a, bf16x8 b, f32x4 c) { return Mma<__bf16>::mma(a, b, c); }
+__device__ inline f32x4 mfma(bf16x4 a, bf16x4 b, f32x4 c) { return Mma<__bf16>::mma4(a, b, c); }
+
+// c += sum over the plane pairs, the smallest first.
+template <int NA, int NB, typename F> __device__ inline void mma_planes(const F (&a)[NA], const F (&b)[NB], f32x4 &c)
+{
+#pragma unroll
+    for (int s = 2; s >= 0; --s) {
+#pragma unroll
+        for (int i = 0; i < NA; ++i) {
+            const int j = s - i;
+            if (j >= 0 && j < NB) c = mfma(a[i], b[j], c);
+        }
+    }
+}
+
+// The scores and the factor's gradient, which the softmax and its pull-back
+// amplify: fp32 elements sum the leading planes' product (hi) apart from the
+// five small ones (lo), so that it takes one rounding a chunk and not six.
+template <bool TWO> struct Score {
+    f32x4 hi, lo;
+    __device__ Score() : hi{0.f, 0.f, 0.f, 0.f}, lo{0.f, 0.f, 0.f, 0.f} {}
+    template <int NA, int NB> __device__ inline void add(const bf16x8 (&a)[NA], const bf16x8 (&b)[NB])
+    {
+        if constexpr (TWO) {
+            hi = mfma(a[0], b[0], hi);
+#pragma unroll
+            for (int s = 2; s >= 1; --s) {
+#pragma unroll
+                for (int i = 0; i < NA; ++i) {
+                    const int j = s - i;
+                    if (j >= 0 && j < NB) lo = mfma(a[i], b[j], lo);
+                }
+            }
+        } else {
+            mma_planes(a, b, hi);
+        }
+    }
+    __device__ inline f32x4 value() const { return TWO ? hi + lo : hi; }
 };
 
-// Cross-lane reductions with no LDS round trip.
+// Operand fragments of the products that contract over KD = 32 or 16 rows or
+// columns of a unit (KD = 16 only where the unit has no more).
+template <int KD> using Frag = typename std::conditional<KD == 32, bf16x8, bf16x4>::type;
+
+// Rows x0 .. x0 + KD - 1 (the contraction index), column c0 + lane % 16, of
+// every plane of a row-major LDS tile: slots 0..3 of lane group g are rows
+// 4g + q, slots 4..7 rows 16 + 4g + q.
+template <int KD, int NP>
+__device__ inline void read_cols(const __bf16 *X, int plane, int ld, int x0, int c0, int lane, Frag<KD> (&f)[NP])
+{
+#pragma unroll
+    for (int a = 0; a < NP; ++a) {
+        const bf16x4 lo = rows4<__bf16>(X + a * plane, ld, x0, c0, lane);
+        if constexpr (KD == 32) {
+            const bf16x4 hi = rows4<__bf16>(X + a * plane, ld, x0 + 16, c0, lane);
+            f[a] = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
+        } else {
+            f[a] = lo;
+        }
+    }
+}
+
+// Columns c0 .. c0 + KD - 1 (the contraction index) of row `row` of every
+// plane, in the slots of read_cols.
+template <int KD, int NP>
+__device__ inline void read_row(const __bf16 *row, int plane, int c0, int g, Frag<KD> (&f)[NP])
+{
+#pragma unroll
+    for (int a = 0; a < NP; ++a) {
+        const __bf16 *src = row + a * plane + c0 + 4 * g;
+        const bf16x4 lo = *reinterpret_cast<const bf16x4 *>(src);
+        if constexpr (KD == 32) {
+            const bf16x4 hi = *reinterpret_cast<const bf16x4 *>(src + 16);
+            f[a] = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
+        } else {
+            f[a] = lo;
+        }
+    }
+}
+
+// Elements 32c + 8g .. + 7 of a row of every plane of an LDS tile (products
+// that contract over the head dimension).
+template <int NP> __device__ inline void read_chunk(const __bf16 *row, int plane, int c, int g, bf16x8 (&f)[NP])
+{
+#pragma unroll
+    for (int a = 0; a < NP; ++a) f[a] = *reinterpret_cast<const bf16x8 *>(row + a * plane + 32 * c + 8 * g);
+}
+
+// A uniform base address with 32-bit byte offsets.  A lane whose `ok` is false
+// takes an offset past the end: its load gives zero and its store is dropped,
+// by the hardware's range check.  No access sits under a branch, so the
+// compiler knows how many are in flight: a wait for the rows fetched a chunk
+// ago does not also wait for the stores issued since.
+struct Span {
+    __amdgpu_buffer_rsrc_t r;
+    static constexpr int kEnd = 0x7fffffff, kDefault = 0x00027000;  // raw, 32-bit data format
+    __device__ explicit Span(const void *base) : r(__builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(base), 0, kEnd, kDefault)) {}
+    __device__ static inline int at(uint32_t bytes, bool ok) { return ok ? (int)bytes : (int)0x80000000u; }
+    __device__ inline u32x4 load16(uint32_t bytes, bool ok) const
+    {
+        return __builtin_amdgcn_raw_buffer_load_b128(r, at(bytes, ok), 0, 0);
+    }
+    __device__ inline f32x4 loadf(uint32_t bytes, bool ok) const
+    {
+        const u32x4 v = load16(bytes, ok);
+        f32x4 f;
+        __builtin_memcpy(&f, &v, 16);
+        return f;
+    }
+    __device__ inline float load1(uint32_t bytes, bool ok) const
+    {
+        return __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(r, at(bytes, ok), 0, 0));
+    }
+    // four elements of E
+    template <typename E> __device__ inline void store(f32x4 v, uint32_t bytes, bool ok) const
+    {
+        if constexpr (sizeof(E) == 4) {
+            u32x4 u;
+            __builtin_memcpy(&u, &v, 16);
+            __builtin_amdgcn_raw_buffer_store_b128(u, r, at(bytes, ok), 0, 0);
+        } else {
+            E e[4] = {to_elem<E>(v[0]), to_elem<E>(v[1]), to_elem<E>(v[2]), to_elem<E>(v[3])};
+            u32x2 u;
+            __builtin_memcpy(&u, e, 8);
+            __builtin_amdgcn_raw_buffer_store_b64(u, r, at(bytes, ok), 0, 0);
+        }
+    }
+};
+
+// read_chunk from row `row` of E, d elements apart, in global memory (!ok: zero),
+// elements >= d zero (d a multiple of 16 bytes' worth).
+template <typename E, int NP> __device__ inline void load_chunk(const Span &s, int row, bool ok, int c, int g, int d, bf16x8 (&f)[NP])
+{
+    constexpr int V = 16 / (int)sizeof(E);
+    E e[8];
+#pragma unroll
+    for (int v = 0; v < 8; v += V) {
+        const int col = 32 * c + 8 * g + v;
+        const u32x4 raw = s.load16((row * d + col) * (uint32_t)sizeof(E), ok && col < d);
+        __builtin_memcpy(e + v, &raw, 16);
+    }
+    if constexpr (NP == 1) {
+        __builtin_memcpy(&f[0], e, 16);
+    } else {
+        float x[8];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) x[i] = static_cast<float>(e[i]);
+        split<NP, 8>(x, f);
+    }
+}
+
+// R rows of D elements of E from global memory into registers (fetch), and
+// from there into the NP planes of an LDS tile of row stride LD (stage), the
+// 16-byte chunks shared out over NTH threads.  Rows >= nr and columns >= nc
+// (a multiple of a chunk) are zero.
+template <typename E, int NP, int R, int D, int LD, int NTH> struct Rows {
+    static constexpr int V = 16 / (int)sizeof(E), CPR = D / V, ALL = R * CPR, CH = (ALL + NTH - 1) / NTH;
+    static constexpr int PLANE = R * LD;
+    u32x4 c[CH];
+
+    // Row r starts `step` elements after row r - 1 (offsets in 32 bits: within a head).
+    __device__ inline void fetch(const E *base, uint32_t step, int nr, int nc, int tid)
+    {
+        const Span s(base);
+#pragma unroll
+        for (int h = 0; h < CH; ++h) {
+            const int idx = tid + h * NTH, r = idx / CPR, col = (idx % CPR) * V;
+            c[h] = s.load16((r * step + col) * (uint32_t)sizeof(E), r < nr && col < nc);  // nr <= R
+        }
+    }
+
+    __device__ inline void stage(__bf16 *X, int tid) const
+    {
+#pragma unroll
+        for (int h = 0; h < CH; ++h) {
+            const int idx = tid + h * NTH, r = idx / CPR, col = (idx % CPR) * V;
+            if (ALL % NTH != 0 && idx >= ALL) break;
+            __bf16 *dst = X + r * LD + col;
+            if constexpr (NP == 1) {
+                *reinterpret_cast<u32x4 *>(dst) = c[h];
+            } else {
+                typedef __bf16 vec __attribute__((ext_vector_type(V)));
+                E e[V];
+                __builtin_memcpy(e, &c[h], 16);
+                float x[V];
+#pragma unroll
+                for (int i = 0; i < V; ++i) x[i] = static_cast<float>(e[i]);
+                vec p[NP];
+                split<NP, V>(x, p);
+#pragma unroll
+                for (int a = 0; a < NP; ++a) *reinterpret_cast<vec *>(dst + a * PLANE) = p[a];
+            }
+        }
+    }
+};
+
+// The four columns 16t + 4g + q that a lane holds of row `row` of a factor, as
+// three planes.
+__device__ inline void store_factor(__bf16 *row, int plane, f32x4 x)
+{
+    const float v[4] = {x[0], x[1], x[2], x[3]};
+    bf16x4 p[3];
+    split<3, 4>(v, p);
+#pragma unroll
+    for (int a = 0; a < 3; ++a) *reinterpret_cast<bf16x4 *>(row + a * plane) = p[a];
+}
+
+// Keeps the compiler from moving LDS reads above this point: hoisted, the
+// operands of all products of a chunk would be live at once.
+__device__ inline void reads_stay() { asm volatile("" ::: "memory"); }
+
+// e^x (x <= 0) in natural units: the pull-backs keep their logits unscaled, so
+// that the rounding of fp32 logits is not added to.
+__device__ inline float exp_nat(float x) { return __builtin_amdgcn_exp2f(x * kLog2e); }
+
+// 1 / x for x >= 1: the hardware reciprocal and one Newton step (to the last bit or so).
+__device__ inline float rcp1(float x)
+{
+    const float r = fast_rcp(x);
+    return __builtin_fmaf(__builtin_fmaf(-x, r, 1.f), r, r);
+}
+
+// What the waves of a unit exchange about a row of a factor p = e^z / sum e^z
+// and its gradient g: of this wave's columns, the maximum of z, the sum of
+// e = e^(z - max), and the sum of e g.  The pull-back needs g - <p, g>, which
+// cancels where one weight dominates: with fp32 elements (REF) a wave gives
+// the mean of g under its own weights and the sum of e (g - mean) instead, so
+// that the differences, and not the values, carry the rounding.
+template <bool REF> struct RowStat {
+    float mx, sum, dot, rest;
+    float scale, mean, fix;  // of the whole row: p = e scale, g - <p, g> = (g - mean) - fix
+
+    // from this lane's columns (the four lane groups of a row hold its wave's)
+    template <int N> __device__ inline void own(float mx_, const f32x4 (&e)[N], const f32x4 (&g)[N])
+    {
+        mx = mx_;
+        sum = dot = rest = 0.f;
+#pragma unroll
+        for (int t = 0; t < N; ++t) {
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                sum += e[t][q];
+                dot = __builtin_fmaf(e[t][q], g[t][q], dot);
+            }
+        }
+        sum = lanegroup_sum(sum);
+        dot = lanegroup_sum(dot);
+        if constexpr (REF) {
+            dot = sum != 0.f ? dot * fast_rcp(sum) : 0.f;  // the mean; NaN stays
+#pragma unroll
+            for (int t = 0; t < N; ++t) {
+#pragma unroll
+                for (int q = 0; q < 4; ++q) rest = __builtin_fmaf(e[t][q], g[t][q] - dot, rest);
+            }
+            rest = lanegroup_sum(rest);
+        }
+    }
+
+    // The row of which this is one of NIG parts (in LDS, `step` apart); g of a
+    // part is g + slope * (its maximum - the row's).  !live: a row of zeros.
+    template <int NIG> __device__ inline void whole(const f32x4 *parts, int step, float slope, bool live)
+    {
+        float M = mx, all = sum, acc = dot, left = rest;
+        if constexpr (NIG > 1) {
+            M = kMasked;
+#pragma unroll
+            for (int x = 0; x < NIG; ++x) M = max_nan(M, parts[x * step][0]);
+            all = acc = left = 0.f;
+#pragma unroll
+            for (int x = 0; x < NIG; ++x) {
+                const f32x4 o = parts[x * step];
+                const float sh = o[1] != 0.f ? o[0] - M : 0.f;  // (NaN too) a part of masked columns only adds nothing
+                const float f = o[1] != 0.f ? exp_nat(sh) : 0.f;
+                all = __builtin_fmaf(f, o[1], all);
+                if constexpr (REF)
+                    acc = __builtin_fmaf(f * o[1], __builtin_fmaf(slope, sh, o[2]), acc);
+                else
+                    acc = __builtin_fmaf(f, __builtin_fmaf(slope * sh, o[1], o[2]), acc);
+            }
+        }
+        const float inv = live ? rcp1(all) : 0.f;
+        mean = (REF && NIG == 1) ? dot : live ? acc * inv : 0.f;
+        if constexpr (REF) {
+            if constexpr (NIG > 1) {
+#pragma unroll
+                for (int x = 0; x < NIG; ++x) {
+                    const f32x4 o = parts[x * step];
+                    const float sh = o[1] != 0.f ? o[0] - M : 0.f;
+                    const float f = o[1] != 0.f ? exp_nat(sh) : 0.f;
+                    left = __builtin_fmaf(f, __builtin_fmaf(o[1], __builtin_fmaf(slope, sh, o[2]) - mean, o[3]), left);
+                }
+            }
+            fix = live ? left * inv : 0.f;
+        } else {
+            fix = 0.f;
+        }
+        mx = NIG > 1 ? mx - M : 0.f;  // this part's maximum less the row's
+        scale = NIG > 1 ? exp_nat(mx) * inv : inv;
+    }
+    __device__ inline float centred(float g) const { return REF ? (g - mean) - fix : g - mean; }
+};
+
+// Sums over the 16 lanes of a row (DPP), every lane ending with the sum.
 template <int CTRL> __device__ inline float dpp(float x)
 {
     return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), CTRL, 0xf, 0xf, false));
 }
-constexpr int kQuadXor1 = 0xB1, kQuadXor2 = 0x4E, kRowHalfMirror = 0x141, kRowMirror = 0x140;
-
-// Sum and max over groups of G consecutive lanes (G = 16, 32 or 64): DPP
-// within rows of 16 lanes, then the permlane swaps across rows as far as the
-// group reaches.  Every lane of a group ends with the group's value.
-template <int G> __device__ inline float group_sum(float x)
+__device__ inline float lanes16_sum(float x)
 {
-    x += dpp<kQuadXor1>(x);
-    x += dpp<kQuadXor2>(x);
-    x += dpp<kRowHalfMirror>(x);
-    x += dpp<kRowMirror>(x);
-    if constexpr (G >= 32) x = wave_xor_sum<16>(x);
-    if constexpr (G >= 64) x = wave_xor_sum<32>(x);
-    return x;
+    x += dpp<0xB1>(x);   // quad: xor 1
+    x += dpp<0x4E>(x);   // quad: xor 2
+    x += dpp<0x141>(x);  // half row mirror
+    return x + dpp<0x140>(x);  // row mirror
 }
 
-template <int G> __device__ inline float group_max(float x)
-{
-    x = max_nan(x, dpp<kQuadXor1>(x));
-    x = max_nan(x, dpp<kQuadXor2>(x));
-    x = max_nan(x, dpp<kRowHalfMirror>(x));
-    x = max_nan(x, dpp<kRowMirror>(x));
-    if constexpr (G >= 32) x = wave_xor_max<16>(x);
-    if constexpr (G >= 64) x = wave_xor_max<32>(x);
-    return x;
-}
-
-// Operands of a product, as LDS tiles with row strides LA, LB:
-//   A(r, k) = TA ? A[k][r] : A[r][k],   B(k, n) = TB ? B[n][k] : B[k][n].
-// MFMA step s of a 16-long chunk k0 hands lane group g = lane/16 the index
-// k0 + 4g + s, so a lane reads four consecutive k at once: one 16-byte read
-// where k is contiguous (A as stored, B transposed), four conflict-free
-// scalar reads otherwise.  The contraction length is a compile-time constant:
-// the loop unrolls, every read is the lane's base address plus an immediate
-// offset, and all reads can be issued ahead of the MFMAs.
-// Four consecutive elements of an LDS tile as floats: one 16-byte read of
-// fp32, or one 8-byte read of 16-bit elements converted exactly.
-template <typename E> __device__ inline void read4(const E *p, float *v)
-{
-    if constexpr (std::is_same<E, float>::value) {
-        const f32x4 x = *reinterpret_cast<const f32x4 *>(p);
-#pragma unroll
-        for (int s = 0; s < 4; ++s) v[s] = x[s];
-    } else {
-        E e[4];
-        *reinterpret_cast<u32x2 *>(e) = *reinterpret_cast<const u32x2 *>(p);
-#pragma unroll
-        for (int s = 0; s < 4; ++s) v[s] = static_cast<float>(e[s]);
-    }
-}
-
-// Operands of a product, as LDS tiles (element types EA, EB: fp32, or the
-// 16-bit element type for the whole-unit tiles of 128 x 128 units) with row
-// strides LA, LB:
-//   A(r, k) = TA ? A[k][r] : A[r][k],   B(k, n) = TB ? B[n][k] : B[k][n].
-template <bool TA, bool TB, int LA, int LB, typename EA = float, typename EB = float> struct Pair {
-    const EA *A;
-    const EB *B;
-
-    // acc += sum_{k < K} A(r, k) B(k, n)
-    template <int K> __device__ void accumulate(f32x4 &acc, int r, int n, int g) const
-    {
-        const EA *pa = TA ? A + 4 * g * LA + r : A + r * LA + 4 * g;
-        const EB *pb = TB ? B + n * LB + 4 * g : B + 4 * g * LB + n;
-#pragma unroll
-        for (int k0 = 0; k0 < K; k0 += 16) {
-            float a[4], b[4];
-            if constexpr (TA) {
-#pragma unroll
-                for (int s = 0; s < 4; ++s) a[s] = static_cast<float>(pa[(k0 + s) * LA]);
-            } else {
-                read4(pa + k0, a);
-            }
-            if constexpr (TB) {
-                read4(pb + k0, b);
-            } else {
-#pragma unroll
-                for (int s = 0; s < 4; ++s) b[s] = static_cast<float>(pb[(k0 + s) * LB]);
-            }
-#pragma unroll
-            for (int s = 0; s < 4; ++s) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a[s], b[s], acc, 0, 0, 0);
-        }
-    }
+// ---------------------------------------------------------------------------------------
+// Shape of a unit: S columns (the tile of b for r_bwd, of m for l_bwd), D the
+// tile width, NP planes of the element type.
+// ---------------------------------------------------------------------------------------
+struct Plan {
+    int C;      // rows of a chunk
+    bool UL;    // the unit's main column operand (K, alpha_L) in LDS instead of registers
+    bool XL;    // l_bwd, t < T: d alpha_R' in LDS instead of registers
+    bool MUX;   // the two factors take turns in one LDS buffer
 };
 
-template <bool TA, bool TB, int LA, int LB, typename EA, typename EB>
-__device__ inline Pair<TA, TB, LA, LB, EA, EB> pair(const EA *A, const EB *B)
-{
-    return Pair<TA, TB, LA, LB, EA, EB>{A, B};
-}
+template <int S, int D, int NP, bool LK, bool LAST> struct Shape {
+    // Two workgroups a compute unit (K in LDS, the factors in turn, 128 VGPRs)
+    // where that needs no spills: r_bwd before the last step at 128 x 64, 126 us
+    // a launch against 178 us with one.  The others at that size hold dY's or
+    // d alpha_R's operands as well and spill at 128 VGPRs: r_bwd of the last
+    // step took 288 us against 212 us with one workgroup, l_bwd 231 against 152.
+    static constexpr bool TWO = S == 128 && D == 64 && NP == 1 && !LK && !LAST;
+    static constexpr int IPW = S >= 64 ? 2 : 1, NIG = S / 16 / IPW;  // column tiles per wave, column groups
+    static constexpr int KDI = S >= 32 ? 32 : 16, NKI = S / KDI;     // contraction over the columns
+    static constexpr int LDX = D + 16, LDP = S + 8;  // LDS rows: operands, factors (bank conflicts: see Ld, LHalf)
+    static constexpr int NC = D / 32, NDT = D / 16;
+    // planes of the row operands (r: alpha_R, d alpha_L and dY; l: Q and dO)
+    static constexpr int PR = LK ? NP * (LAST ? 2 : 1) : NP + 3 + (LAST ? 3 : 0);
+    static constexpr int PX = LK && !LAST ? 3 : NP;  // planes of Y or d alpha_R'
 
-// out(r, c) = sum over the pairs of A(r, :) B(:, c) for r < M, c < N, with
-// contraction K (all multiples of 16, fixed at compile time: the tiles are
-// zero beyond the live rows and columns).  The 16 x 16 output tiles are
-// shared out over the W waves; lane (g, c) of v_mfma_f32_16x16x4f32 receives
-// rows 4g + q, q = 0..3, of column c, and hands each element to
-// st(r, c, value): every element is stored by exactly one lane.
-template <int W, int M, int N, int K, typename Store, typename... P>
-__device__ inline void gemm(int wave, int lane, Store &&st, const P &...pairs)
-{
-    constexpr int tn = N / 16, tiles = (M / 16) * tn;
-    const int g = lane >> 4, c = lane & 15;
-    for (int t = wave; t < tiles; t += W) {
-        const int r0 = (t / tn) * 16, c0 = (t % tn) * 16;
-        f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-        (pairs.template accumulate<K>(acc, r0 + c, c0 + c, g), ...);
-#pragma unroll
-        for (int q = 0; q < 4; ++q) st(r0 + 4 * g + q, c0 + c, acc[q]);
-    }
-}
-
-// An M x N product accumulated over several calls (one per row chunk) in the
-// registers of the waves that own its output tiles: the same tile-to-wave
-// assignment as gemm, each wave holding SLOTS tiles.
-template <int W, int M, int N> struct Acc {
-    static constexpr int TN = N / 16, TILES = (M / 16) * TN, SLOTS = (TILES + W - 1) / W;
-    f32x4 v[SLOTS];
-
-    __device__ void zero()
+    static constexpr int dt2(int) { return (NDT + NIG - 1) / NIG; }  // tiles of the row gradient per wave
+    static constexpr int regs(Plan p)  // VGPRs that live through the unit
     {
-#pragma unroll
-        for (int s = 0; s < SLOTS; ++s) v[s] = f32x4{0.f, 0.f, 0.f, 0.f};
-    }
-
-    template <int K, typename... P> __device__ void add(int wave, int lane, const P &...pairs)
-    {
-        const int g = lane >> 4, c = lane & 15;
-#pragma unroll
-        for (int s = 0; s < SLOTS; ++s) {
-            const int t = wave + s * W;
-            if (t < TILES) {
-                const int r0 = (t / TN) * 16, c0 = (t % TN) * 16;
-                (pairs.template accumulate<K>(v[s], r0 + c, c0 + c, g), ...);
-            }
+        const int njt = p.C / 16, dh = njt;
+        int r = IPW * (NDT / dh) * 4 * (LAST ? 2 : 1);               // accumulators
+        if (!p.UL) r += (IPW * NC + dt2(0) * NKI) * NP * 4;           // K, alpha_L: rows and columns
+        if (LK) {
+            if (!p.XL) r += IPW * NC * PX * 4 + (LAST ? 0 : dt2(0) * NKI * 12);
+            r += IPW * 12;
+        } else if (LAST) {
+            r += IPW * NC * NP * 4;  // V
         }
+        return r;
     }
-
-    template <typename Store> __device__ void store(int wave, int lane, Store &&st) const
+    static constexpr int unit_bytes(Plan p) { return ((p.UL ? NP : 0) + (p.XL ? 3 : 0)) * S * LDX * 2; }
+    static constexpr int rows_bytes(Plan p) { return PR * p.C * LDX * 2; }
+    static constexpr int fact_bytes(Plan p) { return (p.MUX ? 1 : 2) * 3 * p.C * LDP * 2; }
+    static constexpr int stat_bytes(Plan p) { return NIG * p.C * 20 + p.C * 8 + (LK ? S * 8 : 0); }
+    static constexpr int lds_bytes(Plan p)
     {
-        const int g = lane >> 4, c = lane & 15;
-#pragma unroll
-        for (int s = 0; s < SLOTS; ++s) {
-            const int t = wave + s * W;
-            if (t < TILES) {
-                const int r0 = (t / TN) * 16, c0 = (t % TN) * 16;
-#pragma unroll
-                for (int q = 0; q < 4; ++q) st(r0 + 4 * g + q, c0 + c, v[s][q]);
-            }
-        }
+        // the column operands pass through LDS once on their way to registers
+        const int all = unit_bytes(p) + rows_bytes(p) + fact_bytes(p) + stat_bytes(p);
+        const int main = p.UL ? 0 : NP * S * LDX * 2;
+        const int x = LK && !LAST && !p.XL ? unit_bytes(p) + 3 * S * LDX * 2 : 0;
+        return all > main ? (all > x ? all : x) : (main > x ? main : x);
     }
+    // The first plan that fits the LDS and keeps the unit's operands within 168
+    // VGPRs (208 where none does): registers before LDS for the operands (no
+    // reads in the chunk loop), both factors in LDS at once before in turn (two
+    // barriers fewer a chunk), chunks of 32 rows before 16 (a full contraction).
+    static constexpr Plan pick()
+    {
+        if (TWO) return Plan{32, true, false, true};
+        const int cmax = S >= 32 ? 32 : 16;
+        for (int most = 168; most <= 208; most += 40)
+            for (int c = cmax; c >= 16; c /= 2)
+                for (int o = 0; o < 4; ++o)
+                    for (int x = 0; x < 2; ++x) {
+                        const Plan p{c, (o & 2) != 0, (o & 1) != 0, x == 1};
+                        if (p.XL && !(LK && !LAST)) continue;
+                        if (regs(p) <= most && lds_bytes(p) <= 160 * 1024) return p;
+                    }
+        return Plan{0, false, false, false};
+    }
+    static constexpr Plan P = pick();
+    static_assert(P.C > 0, "no plan fits a compute unit");
+    static constexpr int C = P.C, NJT = C / 16, W = NJT * NIG, NTH = 64 * W, KDJ = C;
+    static constexpr int DH = NJT, DTW = NDT / DH;  // head-dimension parts, tiles of one
+    static constexpr int DT2 = dt2(0);
+    static constexpr int PLU = S * LDX, PLR = C * LDX, PLP = C * LDP;  // plane strides
+    static constexpr int LDS_BYTES = lds_bytes(P);
 };
 
-template <int LD> __device__ inline auto to_lds(float *t)
-{
-    return [t](int r, int c, float v) { t[r * LD + c] = v; };
-}
-
-// Rows r < R and columns c < C (compile-time extents, C a multiple of 16;
-// row stride LDT) of an LDS tile from a row-major global matrix of element type E whose
-// row r starts at src(r) (16-byte aligned): element (r, c) is read while
-// r < nr and c < nc (nc a multiple of 16 bytes' worth of elements), zero
-// elsewhere.  One 16-byte global read per chunk.
-template <typename E, int NTH, int R, int C, int LDT, typename Src>
-__device__ inline void load_tile(float *dst, int nr, int nc, Src src, int tid)
-{
-    constexpr int V = 16 / (int)sizeof(E), CPR = C / V;  // elements per chunk, chunks per row
-    for (int idx = tid; idx < R * CPR; idx += NTH) {
-        const int r = idx / CPR, c = (idx % CPR) * V;
-        float v[V];
-        if (r < nr && c < nc) {
-            E e[V];
-            *reinterpret_cast<uint4 *>(e) = *reinterpret_cast<const uint4 *>(src(r) + c);
-#pragma unroll
-            for (int i = 0; i < V; ++i) v[i] = static_cast<float>(e[i]);
-        } else {
-#pragma unroll
-            for (int i = 0; i < V; ++i) v[i] = 0.f;
-        }
-#pragma unroll
-        for (int i = 0; i < V; i += 4)
-            *reinterpret_cast<f32x4 *>(dst + r * LDT + c + i) = f32x4{v[i], v[i + 1], v[i + 2], v[i + 3]};
-    }
-}
-
-// load_tile into a tile of the element type itself (no conversion): rows of
-// C elements at row stride LDT, zero past nr rows and nc columns.
-template <typename E, int NTH, int R, int C, int LDT, typename Src>
-__device__ inline void load_tile_raw(E *dst, int nr, int nc, Src src, int tid)
-{
-    constexpr int V = 16 / (int)sizeof(E), CPR = C / V;
-    static_assert(LDT % V == 0, "16-byte rows");
-    for (int idx = tid; idx < R * CPR; idx += NTH) {
-        const int r = idx / CPR, c = (idx % CPR) * V;
-        uint4 x = {0u, 0u, 0u, 0u};
-        if (r < nr && c < nc) x = *reinterpret_cast<const uint4 *>(src(r) + c);
-        *reinterpret_cast<uint4 *>(dst + r * LDT + c) = x;
-    }
-}
-
-// A whole-unit tile in the element type when HALF, else in fp32.
-template <typename T, int NTH, int R, int C, int LDT, bool HALF, typename U, typename Src>
-__device__ inline void load_unit(U *dst, int nr, int nc, Src src, int tid)
-{
-    if constexpr (HALF)
-        load_tile_raw<T, NTH, R, C, LDT>(dst, nr, nc, src, tid);
-    else
-        load_tile<T, NTH, R, C, LDT>(dst, nr, nc, src, tid);
-}
+// Waves of a unit's workgroup (the launch bound).
+template <typename T, int S, int D, bool LK, bool LAST> constexpr int unit_threads = Shape<S, D, planes_of<T>, LK, LAST>::NTH;
 
 // ---------------------------------------------------------------------------------------
 // The L update of class j of step t undone (LAST: t = T, the update that also
-// produced O).  S >= m; query rows l in chunks of C.
+// produced O).  S >= m: columns k, rows l.
 // ---------------------------------------------------------------------------------------
 template <typename T, int S, int D, bool LAST, bool LENS = false> struct LBwd {
-    using G_ = Geo<S, D, sizeof(T) == 2>;
-    static constexpr int W = G_::W, NTH = G_::NTH, C = G_::C, LS = G_::LS, CPL = G_::CPL, LD = G_::LD;
-    static constexpr int SPAN = G_::SPAN, RPW = G_::RPW;
-    static constexpr bool HALF = G_::HALF;
-    static_assert(!HALF || sizeof(T) == 2, "16-bit unit tiles need 16-bit elements");
-    using UT = typename std::conditional<HALF, T, float>::type;  // alpha_L tile
-    static constexpr int LDU = HALF ? G_::LD16 : LD;
-    static constexpr int UF = S * LDU * (int)sizeof(UT) / 4;  // its floats
-    static constexpr int LDS_FLOATS = UF + S * LD + 2 * C * LD + 2 * C * LS + 2 * S;
+    static constexpr int NP = planes_of<T>;
+    using H = Shape<S, D, NP, true, LAST>;
+    static constexpr Plan P = H::P;
+    static constexpr int IPW = H::IPW, NIG = H::NIG, C = H::C, NJT = H::NJT, NTH = H::NTH, LDX = H::LDX, LDP = H::LDP;
+    static constexpr int PX = H::PX;
+    using KI = Frag<H::KDI>;
+    using KJ = Frag<H::KDJ>;
 
-    __device__ static void run(const BwdBufs<T> &p, const BwdDims &dm, float *lds)
+    __device__ static void run(const BwdBufs<T> &p, const BwdDims &dm, char *lds)
     {
-        const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+        const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, g = lane >> 4, c16 = lane & 15;
+        const int jt = wave % NJT, ig = wave / NJT;
         const int m = dm.m, b = dm.b, n = dm.n, d = dm.d;
         const int64_t bh = blockIdx.x / b;
         const int j = blockIdx.x % b;
@@ -356,338 +554,637 @@ template <typename T, int S, int D, bool LAST, bool LENS = false> struct LBwd {
         const int mk = LENS ? min(m, (nl + b - 1) / b) : m;  // key blocks k < mk hold a real key
         const int64_t Np = (int64_t)m * b, toff = bh * n * d, soff = bh * Np * D, coff = bh * Np;
         const int64_t xoff = bh * Np * d;  // the forward's states: rows of d elements
-        // whole-unit tiles (rows k): alpha_L[j][k]; Y[j][k] (LAST) or d alpha_R'[k][j]
-        UT *aL = reinterpret_cast<UT *>(lds);
-        float *X = lds + UF;
-        // chunk tiles (rows l of the chunk): Qbar, dO (LAST) or L d alpha_R', L, dL then dW
-        float *Qb = X + S * LD, *G = Qb + C * LD, *Lm = G + C * LD, *dL = Lm + C * LS;
-        float *cL = dL + C * LS, *dcR = cL + S;
 
-        load_unit<T, NTH, S, D, LDU, HALF>(aL, m, d, [&](int k) { return p.aL + xoff + ((int64_t)j * m + k) * d; },
-                                           tid);
-        if constexpr (LAST) {
-            load_tile<T, NTH, S, D, LD>(X, m, d, [&](int k) { return p.Y + xoff + ((int64_t)j * m + k) * d; }, tid);
-        } else {
-            load_tile<float, NTH, S, D, LD>(X, m, d, [&](int k) { return p.daR + soff + ((int64_t)k * b + j) * D; },
-                                         tid);
-        }
-        for (int k = tid; k < S; k += NTH) {
-            cL[k] = k < m ? p.cL[coff + (int64_t)k * b + j] : 0.f;
-            dcR[k] = (!LAST && k < m) ? p.dcR[coff + (int64_t)k * b + j] : 0.f;
-        }
-        Acc<W, S, D> daL, dY;  // sums over all rows l
-        daL.zero();
-        if constexpr (LAST) dY.zero();
-        float dcl = 0.f;  // thread k < S: sum over l of dW[l][k]
-        float *dQ = p.dQ + toff + (int64_t)j * d;
+        __bf16 *US = reinterpret_cast<__bf16 *>(lds);           // alpha_L[j] (UL)
+        __bf16 *XS = US + (P.UL ? NP * H::PLU : 0);             // d alpha_R' (XL)
+        __bf16 *Qs = XS + (P.XL ? 3 * H::PLU : 0);              // Qbar rows of the chunk
+        __bf16 *Gs = Qs + NP * H::PLR;                          // dO rows (LAST)
+        __bf16 *Ls = Gs + (LAST ? NP * H::PLR : 0);             // L
+        __bf16 *Ws = P.MUX ? Ls : Ls + 3 * H::PLP;              // dW
+        f32x4 *stat = reinterpret_cast<f32x4 *>(Ws + 3 * H::PLP);  // [NIG][C]
+        float *sums = reinterpret_cast<float *>(stat + NIG * C);   // [NJT][S]
 
-        for (int ch = 0; ch < G_::NCH; ++ch) {
-            const int l0 = ch * C, lc = min(max(ml - l0, 0), C);  // live rows of the chunk
-            load_tile<T, NTH, C, D, LD>(Qb, lc, d, [&](int l) { return p.q + toff + ((int64_t)(l0 + l) * b + j) * d; },
-                                     tid);
-            if constexpr (LAST)
-                load_tile<T, NTH, C, D, LD>(
-                    G, lc, d, [&](int l) { return p.dout + toff + ((int64_t)(l0 + l) * b + j) * d; }, tid);
-            __syncthreads();
+        // Qbar[j], dO of class j: rows step_l apart; rows k of alpha_L[j] and Y[j], d apart, or of d alpha_R'
+        const uint32_t step_l = (uint32_t)b * d;
+        const T *qb = p.q + toff + (int64_t)j * d, *gb = p.dout + toff + (int64_t)j * d;
+        const T *ab = p.aL + xoff + (int64_t)j * m * d, *yb = p.Y + xoff + (int64_t)j * m * d;
+        const float *xb = p.daR + soff + (int64_t)j * D;
+        float *dqb = p.dQ + toff + (int64_t)j * d;
 
-            // unnormalised scores <Qbar[l], alpha_L[k]>
-            gemm<W, C, S, D>(wave, lane, to_lds<LS>(Lm), pair<false, true, LD, LDU>(Qb, aL));
-            __syncthreads();
-            // L[l][k] = softmax_k (s score - c_L[k]): RPW rows l per wave instruction,
-            // SPAN lanes and CPL columns k per lane for each
-            for (int base = wave * RPW; base < C; base += W * RPW) {
-                const int l = base + lane / SPAN, col = lane % SPAN;
-                const bool live = l0 + l < m && (!LENS || mk > 0);  // no real key at all: L = 0
-                float *row = Lm + l * LS;
-                float z[CPL], mx = -INFINITY;
+        // the unit's column operands
+        bf16x8 aF[P.UL ? 1 : IPW][P.UL ? 1 : H::NC][NP], xF[P.XL ? 1 : IPW][P.XL ? 1 : H::NC][PX];
+        KI aT[P.UL ? 1 : H::DT2][P.UL ? 1 : H::NKI][NP];
+        KI xT[LAST || P.XL ? 1 : H::DT2][LAST || P.XL ? 1 : H::NKI][3];
+        Rows<T, NP, S, D, LDX, NTH> ua;
+        ua.fetch(ab, d, m, d, tid);
+        Rows<float, 3, S, D, LDX, NTH> ux;
+        if constexpr (!LAST) ux.fetch(xb, (uint32_t)b * D, m, d, tid);
+        Rows<T, NP, C, D, LDX, NTH> qr, gr;
+        qr.fetch(qb, step_l, min(max(ml, 0), C), d, tid);
+        if constexpr (LAST) gr.fetch(gb, step_l, min(max(ml, 0), C), d, tid);
+        f32x4 cl[IPW], dcr[IPW];  // c_L[j][k], d c_R'[k][j]
 #pragma unroll
-                for (int u = 0; u < CPL; ++u) {
-                    const int k = col + 64 * u;
-                    z[u] = live && k < mk ? dm.s * row[k] - cL[k] : -INFINITY;
-                    mx = max_nan(mx, z[u]);
-                }
-                mx = group_max<SPAN>(mx);
-                float sum = 0.f;
+        for (int t = 0; t < IPW; ++t) {
 #pragma unroll
-                for (int u = 0; u < CPL; ++u) {
-                    z[u] = live && col + 64 * u < mk ? __expf(z[u] - mx) : 0.f;
-                    sum += z[u];
-                }
-                sum = group_sum<SPAN>(sum);
-                const float inv = live ? 1.f / sum : 0.f;  // rows past m: all zero
-#pragma unroll
-                for (int u = 0; u < CPL; ++u)
-                    if (col + 64 * u < S) row[col + 64 * u] = z[u] * inv;
+            for (int q = 0; q < 4; ++q) {
+                const int k = (ig * IPW + t) * 16 + 4 * g + q;
+                cl[t][q] = Span(p.cL + coff + j).load1((uint32_t)(k * b) * 4, k < m);
+                dcr[t][q] = 0.f;
+                if constexpr (!LAST) dcr[t][q] = Span(p.dcR + coff + j).load1((uint32_t)(k * b) * 4, k < m);
             }
-            __syncthreads();
-
+            const int k = (ig * IPW + t) * 16 + c16;
             if constexpr (LAST) {
-                // dL = dO Y^T;  dY += L^T dO
-                gemm<W, C, S, D>(wave, lane, to_lds<LS>(dL), pair<false, true, LD, LD>(G, X));
-                dY.template add<C>(wave, lane, pair<true, false, LS, LD>(Lm, G));
-            } else {
-                // dL = Qbar d alpha_R'^T (+ d c_R' below);  G = L d alpha_R' (the alpha_R' term of dQbar)
-                gemm<W, C, S, D>(wave, lane, to_lds<LS>(dL), pair<false, true, LD, LD>(Qb, X));
-                gemm<W, C, D, S>(wave, lane, to_lds<LD>(G), pair<false, false, LS, LD>(Lm, X));
+#pragma unroll
+                for (int c = 0; c < H::NC; ++c) load_chunk<T>(Span(yb), k, k < m, c, g, d, xF[t][c]);
+            }
+        }
+        if constexpr (P.UL) {
+            ua.stage(US, tid);
+        } else {
+            __bf16 *As = US;
+            ua.stage(As, tid);
+            __syncthreads();
+#pragma unroll
+            for (int t = 0; t < IPW; ++t) {
+#pragma unroll
+                for (int c = 0; c < H::NC; ++c) read_chunk<NP>(As + ((ig * IPW + t) * 16 + c16) * LDX, H::PLU, c, g, aF[t][c]);
+            }
+#pragma unroll
+            for (int x = 0; x < H::DT2; ++x) {
+                const int dt = min(ig + x * NIG, H::NDT - 1);
+#pragma unroll
+                for (int c = 0; c < H::NKI; ++c) read_cols<H::KDI, NP>(As, H::PLU, LDX, H::KDI * c, 16 * dt, lane, aT[x][c]);
             }
             __syncthreads();
-            // dW = s L (dL - <L, dL>), in place of dL
-            for (int base = wave * RPW; base < C; base += W * RPW) {
-                const int l = base + lane / SPAN, col = lane % SPAN;
-                float *lr = Lm + l * LS, *wr = dL + l * LS;
-                float pk[CPL], w[CPL], dot = 0.f;
+        }
+        if constexpr (!LAST) {
+            if constexpr (P.XL) {
+                ux.stage(XS, tid);
+            } else {
+                ux.stage(Qs, tid);
+                __syncthreads();
 #pragma unroll
-                for (int u = 0; u < CPL; ++u) {
-                    const int k = col + 64 * u;
-                    pk[u] = k < S ? lr[k] : 0.f;
-                    w[u] = k < S ? wr[k] + dcR[k] : 0.f;
-                    dot += pk[u] * w[u];
+                for (int t = 0; t < IPW; ++t) {
+#pragma unroll
+                    for (int c = 0; c < H::NC; ++c) read_chunk<3>(Qs + ((ig * IPW + t) * 16 + c16) * LDX, H::PLU, c, g, xF[t][c]);
                 }
-                dot = group_sum<SPAN>(dot);
 #pragma unroll
-                for (int u = 0; u < CPL; ++u)
-                    if (col + 64 * u < S) wr[col + 64 * u] = dm.s * pk[u] * (w[u] - dot);
+                for (int x = 0; x < H::DT2; ++x) {
+                    const int dt = min(ig + x * NIG, H::NDT - 1);
+#pragma unroll
+                    for (int c = 0; c < H::NKI; ++c) read_cols<H::KDI, 3>(Qs, H::PLU, LDX, H::KDI * c, 16 * dt, lane, xT[x][c]);
+                }
+                __syncthreads();
+            }
+        }
+
+        f32x4 daL[IPW][H::DTW], dY[LAST ? IPW : 1][LAST ? H::DTW : 1];  // d alpha_L^T, dY^T: sums over all rows l
+        f32x4 dcl[IPW];                                                 // sums over this lane's rows of dW
+#pragma unroll
+        for (int t = 0; t < IPW; ++t) {
+            dcl[t] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int x = 0; x < H::DTW; ++x) {
+                daL[t][x] = f32x4{0.f, 0.f, 0.f, 0.f};
+                if constexpr (LAST) dY[t][x] = f32x4{0.f, 0.f, 0.f, 0.f};
+            }
+        }
+
+        for (int l0 = 0; l0 < m; l0 += C) {
+            const int lc = min(max(ml - l0, 0), C);  // live rows of the chunk
+            qr.stage(Qs, tid);
+            if constexpr (LAST) gr.stage(Gs, tid);
+            __syncthreads();
+            // this lane's part of dQ's tiles, to be added to
+            const int l = jt * 16 + c16;
+            const Span dqs(dqb + (int64_t)l0 * step_l);
+            f32x4 dqo[H::DT2];
+            if constexpr (!LAST) {
+#pragma unroll
+                for (int x = 0; x < H::DT2; ++x) {
+                    const int e = 16 * (ig + x * NIG) + 4 * g;
+                    dqo[x] = dqs.loadf((l * step_l + e) * 4, l < lc && e < d);
+                }
+            }
+            {  // past the last chunk: every load out of range, no traffic
+                const int l1 = l0 + C, nn = min(max(ml - l1, 0), C);
+                qr.fetch(qb + (int64_t)l1 * step_l, step_l, nn, d, tid);
+                if constexpr (LAST) gr.fetch(gb + (int64_t)l1 * step_l, step_l, nn, d, tid);
+            }
+
+            // scores <alpha_L[k], Qbar[l]> and dL = Y . dO or d alpha_R' . Qbar (lane: k = 16t + 4g + q of row l)
+            f32x4 z[IPW], w[IPW];
+            Score<NP == 3> zs[IPW], ws[IPW];
+#pragma unroll
+            for (int c = 0; c < H::NC; ++c) {
+                bf16x8 qf[NP], gf[NP];
+                reads_stay();
+                read_chunk<NP>(Qs + (jt * 16 + c16) * LDX, H::PLR, c, g, qf);
+                if constexpr (LAST) read_chunk<NP>(Gs + (jt * 16 + c16) * LDX, H::PLR, c, g, gf);
+#pragma unroll
+                for (int t = 0; t < IPW; ++t) {
+                    const int r = ((ig * IPW + t) * 16 + c16) * LDX;
+                    if constexpr (P.UL) {
+                        bf16x8 f[NP];
+                        read_chunk<NP>(US + r, H::PLU, c, g, f);
+                        zs[t].add(f, qf);
+                    } else {
+                        zs[t].add(aF[t][c], qf);
+                    }
+                    if constexpr (LAST) {
+                        ws[t].add(xF[t][c], gf);
+                    } else if constexpr (P.XL) {
+                        bf16x8 f[3];
+                        read_chunk<3>(XS + r, H::PLU, c, g, f);
+                        ws[t].add(f, qf);
+                    } else {
+                        ws[t].add(xF[t][c], qf);
+                    }
+                }
+            }
+#pragma unroll
+            for (int t = 0; t < IPW; ++t) z[t] = zs[t].value(), w[t] = ws[t].value();
+            // L = softmax_k(s score - c_L) and its pull-back
+            float mx = kMasked;
+#pragma unroll
+            for (int t = 0; t < IPW; ++t) {
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    z[t][q] = __builtin_fmaf(z[t][q], dm.s, -cl[t][q]);
+                    w[t][q] += dcr[t][q];
+                    if ((ig * IPW + t) * 16 + 4 * g + q < mk) mx = max_nan(mx, z[t][q]);
+                }
+            }
+            mx = wave_xor_max<32>(wave_xor_max<16>(mx));
+#pragma unroll
+            for (int t = 0; t < IPW; ++t) {
+#pragma unroll
+                for (int q = 0; q < 4; ++q)
+                    z[t][q] = (ig * IPW + t) * 16 + 4 * g + q < mk ? exp_nat(z[t][q] - mx) : 0.f;
+            }
+            RowStat<NP == 3> st;
+            st.own(mx, z, w);
+            const bool live = l0 + jt * 16 + c16 < m && (!LENS || mk > 0);  // rows past m, no real key: L = 0
+            if constexpr (NIG > 1) {
+                if (g == 0) stat[ig * C + jt * 16 + c16] = f32x4{st.mx, st.sum, st.dot, st.rest};
+                __syncthreads();
+            }
+            st.template whole<NIG>(stat + jt * 16 + c16, C, 0.f, live);
+            __bf16 *lrow = Ls + (jt * 16 + c16) * LDP, *wrow = Ws + (jt * 16 + c16) * LDP;
+#pragma unroll
+            for (int t = 0; t < IPW; ++t) {
+                const int k = (ig * IPW + t) * 16 + 4 * g;
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    z[t][q] *= st.scale;                                  // L
+                    w[t][q] = dm.s * z[t][q] * st.centred(w[t][q]);  // dW
+                }
+                dcl[t] += w[t];
+                store_factor(lrow + k, H::PLP, z[t]);
+                if constexpr (!P.MUX) store_factor(wrow + k, H::PLP, w[t]);
             }
             __syncthreads();
 
-            // dQ rows (l0 + l)*b + j: dW alpha_L (+ L d alpha_R')
-            gemm<W, C, D, S>(
-                wave, lane,
-                [&](int l, int e, float v) {
-                    if (l < lc && e < d) {
-                        float *o = dQ + (int64_t)(l0 + l) * b * d + e;
-                        if constexpr (LAST) {
-                            *o = v;
+            f32x4 dq[H::DT2];  // dQbar^T tiles (dt, jt)
+#pragma unroll
+            for (int x = 0; x < H::DT2; ++x) dq[x] = f32x4{0.f, 0.f, 0.f, 0.f};
+            if constexpr (LAST) {
+                // dY[k] += sum_l L[l][k] dO[l]
+                KJ lf[IPW][3];
+#pragma unroll
+                for (int t = 0; t < IPW; ++t) read_cols<H::KDJ, 3>(Ls, H::PLP, LDP, 0, (ig * IPW + t) * 16, lane, lf[t]);
+#pragma unroll
+                for (int x = 0; x < H::DTW; ++x) {
+                    KJ f[NP];
+                    reads_stay();
+                    read_cols<H::KDJ, NP>(Gs, H::PLR, LDX, 0, (jt * H::DTW + x) * 16, lane, f);
+#pragma unroll
+                    for (int t = 0; t < IPW; ++t) mma_planes(f, lf[t], dY[t][x]);
+                }
+            } else {
+                // dQbar[l] += sum_k L[l][k] d alpha_R'[k]
+#pragma unroll
+                for (int c = 0; c < H::NKI; ++c) {
+                    KI r[3];
+                    reads_stay();
+                    read_row<H::KDI, 3>(lrow, H::PLP, H::KDI * c, g, r);
+#pragma unroll
+                    for (int x = 0; x < H::DT2; ++x) {
+                        if (H::DT2 * NIG > H::NDT && ig + x * NIG >= H::NDT) continue;
+                        if constexpr (P.XL) {
+                            KI f[3];
+                            read_cols<H::KDI, 3>(XS, H::PLU, LDX, H::KDI * c, 16 * min(ig + x * NIG, H::NDT - 1), lane, f);
+                            mma_planes(f, r, dq[x]);
                         } else {
-                            *o += v + G[l * LD + e];
+                            mma_planes(xT[x][c], r, dq[x]);
                         }
                     }
-                },
-                pair<false, false, LS, LDU>(dL, aL));
-            // d alpha_L[k] += dW^T Qbar;  d c_L[k] += sum_l dW[l][k]
-            daL.template add<C>(wave, lane, pair<true, false, LS, LD>(dL, Qb));
-            if (tid < S) {
-                for (int l = 0; l < C; ++l) dcl += dL[l * LS + tid];
+                }
             }
-            __syncthreads();  // the next chunk overwrites the chunk tiles
+            if constexpr (P.MUX) {
+                __syncthreads();
+#pragma unroll
+                for (int t = 0; t < IPW; ++t) store_factor(wrow + (ig * IPW + t) * 16 + 4 * g, H::PLP, w[t]);
+                __syncthreads();
+            }
+            // d alpha_L[k] += sum_l dW[l][k] Qbar[l]
+            {
+                KJ wf[IPW][3];
+#pragma unroll
+                for (int t = 0; t < IPW; ++t) read_cols<H::KDJ, 3>(Ws, H::PLP, LDP, 0, (ig * IPW + t) * 16, lane, wf[t]);
+#pragma unroll
+                for (int x = 0; x < H::DTW; ++x) {
+                    KJ f[NP];
+                    reads_stay();
+                    read_cols<H::KDJ, NP>(Qs, H::PLR, LDX, 0, (jt * H::DTW + x) * 16, lane, f);
+#pragma unroll
+                    for (int t = 0; t < IPW; ++t) mma_planes(f, wf[t], daL[t][x]);
+                }
+            }
+            // dQbar[l] += sum_k dW[l][k] alpha_L[k]
+#pragma unroll
+            for (int c = 0; c < H::NKI; ++c) {
+                KI r[3];
+                reads_stay();
+                read_row<H::KDI, 3>(wrow, H::PLP, H::KDI * c, g, r);
+#pragma unroll
+                for (int x = 0; x < H::DT2; ++x) {
+                    if (H::DT2 * NIG > H::NDT && ig + x * NIG >= H::NDT) continue;
+                    if constexpr (P.UL) {
+                        KI f[NP];
+                        read_cols<H::KDI, NP>(US, H::PLU, LDX, H::KDI * c, 16 * min(ig + x * NIG, H::NDT - 1), lane, f);
+                        mma_planes(f, r, dq[x]);
+                    } else {
+                        mma_planes(aT[x][c], r, dq[x]);
+                    }
+                }
+            }
+#pragma unroll
+            for (int x = 0; x < H::DT2; ++x) {
+                const int e = 16 * (ig + x * NIG) + 4 * g;  // (tiles past the last have e >= D >= d)
+                f32x4 v = dq[x];
+                if constexpr (!LAST) v += dqo[x];
+                dqs.template store<float>(v, (l * step_l + e) * 4, l < lc && e < d);
+            }
+            __syncthreads();  // the next chunk overwrites the rows and factors
         }
 
-        float *daLg = p.daL + soff + (int64_t)j * m * D;
-        daL.store(wave, lane, [&](int k, int e, float v) {
-            if (k < m && e < d) daLg[(int64_t)k * D + e] = v;
-        });
-        if constexpr (LAST) {
-            float *dYg = p.dY + soff + (int64_t)j * m * D;
-            dY.store(wave, lane, [&](int k, int e, float v) {
-                if (k < m && e < d) dYg[(int64_t)k * D + e] = v;
-            });
+#pragma unroll
+        for (int t = 0; t < IPW; ++t) {
+            const int k = (ig * IPW + t) * 16 + c16;
+#pragma unroll
+            for (int x = 0; x < H::DTW; ++x) {
+                const int e = (jt * H::DTW + x) * 16 + 4 * g;
+                const int64_t u = soff + (int64_t)j * m * D;
+                const uint32_t o = (k * D + e) * 4;
+                Span(p.daL + u).store<float>(daL[t][x], o, k < m && e < d);
+                if constexpr (LAST) Span(p.dY + u).store<float>(dY[t][x], o, k < m && e < d);
+            }
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const float v = lanes16_sum(dcl[t][q]);
+                if (c16 == 0) sums[jt * S + (ig * IPW + t) * 16 + 4 * g + q] = v;
+            }
         }
-        if (tid < m) p.dcL[coff + (int64_t)j * m + tid] = -dcl / dm.s;
+        __syncthreads();
+        for (int k = tid; k < m; k += NTH) {
+            float v = sums[k];
+            if constexpr (NJT > 1) v += sums[S + k];
+            p.dcL[coff + (int64_t)j * m + k] = -v / dm.s;
+        }
     }
 };
 
 // ---------------------------------------------------------------------------------------
 // The R update of block k of step t undone (FIRST: t = 1, LAST: t = T).
-// S >= b; rows j in chunks of C.
+// S >= b: columns i (keys), rows j.
 // ---------------------------------------------------------------------------------------
 template <typename T, int S, int D, bool FIRST, bool LAST, bool LENS = false> struct RBwd {
-    using G_ = Geo<S, D, sizeof(T) == 2>;
-    static constexpr int W = G_::W, NTH = G_::NTH, C = G_::C, LS = G_::LS, CPL = G_::CPL, LD = G_::LD;
-    static constexpr int SPAN = G_::SPAN, RPW = G_::RPW;
-    static constexpr bool HALF = G_::HALF;
-    static_assert(!HALF || sizeof(T) == 2, "16-bit unit tiles need 16-bit elements");
-    using UT = typename std::conditional<HALF, T, float>::type;  // K and V tiles
-    static constexpr int LDU = HALF ? G_::LD16 : LD;
-    static constexpr int UF = S * LDU * (int)sizeof(UT) / 4;  // floats of one
-    static constexpr int LDS_FLOATS = (LAST ? 2 : 1) * UF + (LAST ? 3 : 2) * C * LD + 2 * C * LS + 2 * C;
+    static constexpr int NP = planes_of<T>;
+    using H = Shape<S, D, NP, false, LAST>;
+    static constexpr Plan P = H::P;
+    static constexpr int IPW = H::IPW, NIG = H::NIG, C = H::C, NJT = H::NJT, NTH = H::NTH, LDX = H::LDX, LDP = H::LDP;
+    using KI = Frag<H::KDI>;
+    using KJ = Frag<H::KDJ>;
 
-    __device__ static void run(const BwdBufs<T> &p, const BwdDims &dm, float *lds)
+    __device__ static void run(const BwdBufs<T> &p, const BwdDims &dm, char *lds)
     {
-        const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+        const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, g = lane >> 4, c16 = lane & 15;
+        const int jt = wave % NJT, ig = wave / NJT;
         const int m = dm.m, b = dm.b, n = dm.n, d = dm.d;
         const int64_t bh = blockIdx.x / m;
         const int k = blockIdx.x % m;
-        const int kn = min(b, n - k * b);                                // rows of block k in memory
+        const int kn = min(b, n - k * b);                              // rows of block k in memory
         const int kv = LENS ? min(b, live_rows(dm, bh) - k * b) : kn;  // real keys (and query rows); <= 0: none
         const int64_t Np = (int64_t)m * b, toff = bh * n * d, soff = bh * Np * D, coff = bh * Np;
         const int64_t xoff = bh * Np * d;     // the forward's states: rows of d elements
         const int64_t row0 = (int64_t)k * b;  // first row of block k
-        // whole-unit tiles (rows i): Kbar, Vbar (LAST)
-        UT *Kb = reinterpret_cast<UT *>(lds), *Vb = Kb + S * LDU;
-        // chunk tiles (rows j of the chunk): alpha_R, d alpha_L, dY (LAST), R, dR then dZ s / c_R
-        float *aR = lds + (LAST ? 2 : 1) * UF, *dA = aR + C * LD, *dYt = dA + C * LD;
-        float *Rm = dA + (LAST ? 2 : 1) * C * LD, *dR = Rm + C * LS;
-        float *cR = dR + C * LS, *dcL = cR + C;
 
-        load_unit<T, NTH, S, D, LDU, HALF>(Kb, kv, d, [&](int i) { return p.k + toff + (row0 + i) * d; }, tid);
-        if constexpr (LAST)
-            load_unit<T, NTH, S, D, LDU, HALF>(Vb, kv, d, [&](int i) { return p.v + toff + (row0 + i) * d; }, tid);
-        Acc<W, S, D> dK, dV;  // sums over all rows j
-        dK.zero();
-        if constexpr (LAST) dV.zero();
+        __bf16 *US = reinterpret_cast<__bf16 *>(lds);           // Kbar[k] (UL)
+        __bf16 *As = US + (P.UL ? NP * H::PLU : 0);             // alpha_R rows of the chunk (Q at t = 1)
+        __bf16 *Ds = As + NP * H::PLR;                          // d alpha_L rows
+        __bf16 *Ys = Ds + 3 * H::PLR;                           // dY rows (LAST)
+        __bf16 *Rs = Ys + (LAST ? 3 * H::PLR : 0);              // R
+        __bf16 *Zs = P.MUX ? Rs : Rs + 3 * H::PLP;              // dZ s / c_R
+        f32x4 *stat = reinterpret_cast<f32x4 *>(Zs + 3 * H::PLP);  // [NIG][C]
+        float *part = reinterpret_cast<float *>(stat + NIG * C);   // [NIG][C]
+        float *cRs = part + NIG * C, *dcLs = cRs + C;              // c_R, d c_L of the chunk's rows
 
-        for (int ch = 0; ch < G_::NCH; ++ch) {
-            const int j0 = ch * C;
-            const int jb = min(max(b - j0, 0), C), jq = min(max(kv - j0, 0), C);  // live rows; rows of Q (t = 1)
-            const int jn = min(max(kn - j0, 0), C);                                // rows of dq in memory (t = 1)
-            if constexpr (FIRST) {
-                load_tile<T, NTH, C, D, LD>(aR, jq, d, [&](int jj) { return p.q + toff + (row0 + j0 + jj) * d; }, tid);
-            } else {
-                load_tile<T, NTH, C, D, LD>(aR, jb, d, [&](int jj) { return p.aR + xoff + (row0 + j0 + jj) * d; },
-                                         tid);
-            }
-            load_tile<float, NTH, C, D, LD>(
-                dA, jb, d, [&](int jj) { return p.daL + soff + ((int64_t)(j0 + jj) * m + k) * D; }, tid);
-            if constexpr (LAST)
-                load_tile<float, NTH, C, D, LD>(
-                    dYt, jb, d, [&](int jj) { return p.dY + soff + ((int64_t)(j0 + jj) * m + k) * D; }, tid);
-            for (int jj = tid; jj < C; jj += NTH) {
-                cR[jj] = (FIRST || jj >= jb) ? 1.f : p.cR[coff + (int64_t)(j0 + jj) * m + k];
-                dcL[jj] = jj < jb ? p.dcL[coff + (int64_t)(j0 + jj) * m + k] : 0.f;
-            }
-            __syncthreads();
+        // rows j of alpha_R[k] (Q at t = 1), d apart; of d alpha_L and dY, step_j apart
+        const uint32_t step_j = (uint32_t)m * D;
+        const T *ab = FIRST ? p.q + toff + row0 * d : p.aR + xoff + row0 * d;
+        const T *kb = p.k + toff + row0 * d, *vb = p.v + toff + row0 * d;
+        const float *db = p.daL + soff + (int64_t)k * D, *yb = p.dY + soff + (int64_t)k * D;
+        const int na = FIRST ? kv : b;  // rows of alpha_R
 
-            // unnormalised scores <alpha_R[j], Kbar[i]>;  dR = d alpha_L Kbar^T (+ dY Vbar^T)
-            gemm<W, C, S, D>(wave, lane, to_lds<LS>(Rm), pair<false, true, LD, LDU>(aR, Kb));
-            if constexpr (LAST) {
-                gemm<W, C, S, D>(wave, lane, to_lds<LS>(dR), pair<false, true, LD, LDU>(dA, Kb),
-                                 pair<false, true, LD, LDU>(dYt, Vb));
-            } else {
-                gemm<W, C, S, D>(wave, lane, to_lds<LS>(dR), pair<false, true, LD, LDU>(dA, Kb));
+        // the unit's column operands
+        bf16x8 kF[P.UL ? 1 : IPW][P.UL ? 1 : H::NC][NP], vF[LAST ? IPW : 1][LAST ? H::NC : 1][NP];
+        KI kT[P.UL ? 1 : H::DT2][P.UL ? 1 : H::NKI][NP];
+        Rows<T, NP, S, D, LDX, NTH> uk;
+        uk.fetch(kb, d, max(kv, 0), d, tid);
+        Rows<T, NP, C, D, LDX, NTH> ar;
+        Rows<float, 3, C, D, LDX, NTH> dr, yr;
+        float crr = 1.f, dclr = 0.f;
+        auto fetch = [&](int j0) {
+            const int jb = min(b - j0, C);
+            ar.fetch(ab + (int64_t)j0 * d, d, min(max(na - j0, 0), C), d, tid);
+            dr.fetch(db + (int64_t)j0 * step_j, step_j, jb, d, tid);
+            if constexpr (LAST) yr.fetch(yb + (int64_t)j0 * step_j, step_j, jb, d, tid);
+            const int64_t u = coff + (int64_t)j0 * m + k;
+            crr = 1.f;
+            if constexpr (!FIRST) {
+                crr = Span(p.cR + u).load1((uint32_t)(tid * m) * 4, tid < jb);
+                if (tid >= jb) crr = 1.f;
             }
-            __syncthreads();
-            // per row j (RPW rows per wave instruction, SPAN lanes and CPL keys i per
-            // lane for each): R, then dZ scaled by s / c_R[j] in place of dR
-            for (int base = wave * RPW; base < C; base += W * RPW) {
-                const int jj = base + lane / SPAN, col = lane % SPAN;
-                const bool live = jj < jb && (!LENS || kv > 0);  // a block of padding only has R = 0
-                float *rr = Rm + jj * LS, *dr = dR + jj * LS;
-                const float sc = (!LENS || live) ? dm.s / cR[jj] : 0.f;  // c_R = 1 past the rows j < b
-                float z[CPL], mx = -INFINITY;
-#pragma unroll
-                for (int u = 0; u < CPL; ++u) {
-                    const int i = col + 64 * u;
-                    z[u] = live && i < kv ? sc * rr[i] : -INFINITY;
-                    mx = max_nan(mx, z[u]);
-                }
-                mx = group_max<SPAN>(mx);
-                if (!live) mx = 0.f;  // rows past b: every term below is zero
-                float e[CPL], sum = 0.f;
-#pragma unroll
-                for (int u = 0; u < CPL; ++u) {
-                    e[u] = live && col + 64 * u < kv ? __expf(z[u] - mx) : 0.f;
-                    sum += e[u];
-                }
-                sum = group_sum<SPAN>(sum);
-                const float lsum = live ? __logf(sum) : 0.f, inv = live ? 1.f / sum : 0.f;
-                float r[CPL], logr[CPL], g[CPL], dot = 0.f;
-#pragma unroll
-                for (int u = 0; u < CPL; ++u) {
-                    const int i = col + 64 * u;
-                    const bool on = live && i < kv;
-                    r[u] = e[u] * inv;
-                    logr[u] = on ? z[u] - mx - lsum : 0.f;
-                    g[u] = on ? dr[i] + dcL[jj] * (logr[u] + 1.f) : 0.f;
-                    dot += r[u] * g[u];
-                }
-                dot = group_sum<SPAN>(dot);
-                float dzlog = 0.f;
-#pragma unroll
-                for (int u = 0; u < CPL; ++u) {
-                    const int i = col + 64 * u;
-                    const float dz = r[u] * (g[u] - dot);
-                    dzlog += dz * logr[u];
-                    if (i < S) {
-                        rr[i] = r[u];
-                        dr[i] = dz * sc;
-                    }
-                }
-                dzlog = group_sum<SPAN>(dzlog);
-                if (!FIRST && jj < jb && col == 0)  // zero for a block of padding only (read by l_bwd)
-                    p.dcR[coff + row0 + j0 + jj] = (!LENS || live) ? -dzlog / cR[jj] : 0.f;
-            }
-            __syncthreads();
-
-            // d alpha_R[j] = sum_i dZs[j][i] Kbar[i]: to the workspace, or at step 1 into dq
-            if constexpr (FIRST) {
-                const float *dQ = p.dQ + toff + (row0 + j0) * d;
-                T *dq = p.dq + toff + (row0 + j0) * d;
-                gemm<W, C, D, S>(
-                    wave, lane,
-                    [&](int jj, int e, float v) {  // rows past the length: zero
-                        if (jj < (LENS ? jn : jq) && e < d)
-                            dq[(int64_t)jj * d + e] =
-                                static_cast<T>((!LENS || jj < jq) ? dQ[(int64_t)jj * d + e] + v : 0.f);
-                    },
-                    pair<false, false, LS, LDU>(dR, Kb));
-            } else {
-                float *daR = p.daR + soff + (row0 + j0) * D;
-                gemm<W, C, D, S>(
-                    wave, lane,
-                    [&](int jj, int e, float v) {
-                        if (jj < jb && e < d) daR[(int64_t)jj * D + e] = v;
-                    },
-                    pair<false, false, LS, LDU>(dR, Kb));
-            }
-            // dKbar[i] += sum_j R[j][i] d alpha_L[j] + dZs[j][i] alpha_R[j];  dVbar[i] += sum_j R[j][i] dY[j]
-            dK.template add<C>(wave, lane, pair<true, false, LS, LD>(Rm, dA), pair<true, false, LS, LD>(dR, aR));
-            if constexpr (LAST) dV.template add<C>(wave, lane, pair<true, false, LS, LD>(Rm, dYt));
-            __syncthreads();  // the next chunk overwrites the chunk tiles
-        }
-
-        {
-            float *dKg = p.dK + toff + row0 * d;
-            T *dk = p.dk + toff + row0 * d;
-            dK.store(wave, lane, [&](int i, int e, float v) {
-                if (i < (LENS && FIRST ? kn : kv) && e < d) {  // at t = 1 rows past the length get zero
-                    const int64_t o = (int64_t)i * d + e;
-                    const float acc = (LENS && i >= kv) ? 0.f : LAST ? v : v + dKg[o];
-                    if constexpr (FIRST) {
-                        dk[o] = static_cast<T>(acc);
-                    } else {
-                        dKg[o] = acc;
-                    }
-                }
-            });
-        }
+            dclr = Span(p.dcL + u).load1((uint32_t)(tid * m) * 4, tid < jb);
+        };
+        fetch(0);
         if constexpr (LAST) {
-            T *dv = p.dv + toff + row0 * d;
-            dV.store(wave, lane, [&](int i, int e, float v) {
-                if (i < (LENS ? kn : kv) && e < d) dv[(int64_t)i * d + e] = static_cast<T>((!LENS || i < kv) ? v : 0.f);
-            });
+#pragma unroll
+            for (int t = 0; t < IPW; ++t) {
+                const int i = (ig * IPW + t) * 16 + c16;
+#pragma unroll
+                for (int c = 0; c < H::NC; ++c)
+                    load_chunk<T>(Span(vb), i, i < kv, c, g, d, vF[t][c]);
+            }
+        }
+        if constexpr (P.UL) {
+            uk.stage(US, tid);
+        } else {
+            uk.stage(As, tid);
+            __syncthreads();
+#pragma unroll
+            for (int t = 0; t < IPW; ++t) {
+#pragma unroll
+                for (int c = 0; c < H::NC; ++c) read_chunk<NP>(As + ((ig * IPW + t) * 16 + c16) * LDX, H::PLU, c, g, kF[t][c]);
+            }
+#pragma unroll
+            for (int x = 0; x < H::DT2; ++x) {
+                const int dt = min(ig + x * NIG, H::NDT - 1);
+#pragma unroll
+                for (int c = 0; c < H::NKI; ++c) read_cols<H::KDI, NP>(As, H::PLU, LDX, H::KDI * c, 16 * dt, lane, kT[x][c]);
+            }
+            __syncthreads();
+        }
+
+        f32x4 dK[IPW][H::DTW], dV[LAST ? IPW : 1][LAST ? H::DTW : 1];  // dKbar^T, dVbar^T: sums over all rows j
+#pragma unroll
+        for (int t = 0; t < IPW; ++t) {
+#pragma unroll
+            for (int x = 0; x < H::DTW; ++x) {
+                dK[t][x] = f32x4{0.f, 0.f, 0.f, 0.f};
+                if constexpr (LAST) dV[t][x] = f32x4{0.f, 0.f, 0.f, 0.f};
+            }
+        }
+
+        for (int j0 = 0; j0 < b; j0 += C) {
+            const int jb = min(b - j0, C);                   // rows of the chunk
+            const int jq = min(max(kv - j0, 0), C);          // rows of Q (t = 1)
+            const int jn = min(max(kn - j0, 0), C);          // rows of dq in memory (t = 1)
+            ar.stage(As, tid);
+            dr.stage(Ds, tid);
+            if constexpr (LAST) yr.stage(Ys, tid);
+            if (tid < C) cRs[tid] = crr, dcLs[tid] = dclr;
+            __syncthreads();
+            const int jj = jt * 16 + c16;
+            f32x4 dqo[FIRST ? H::DT2 : 1];  // this lane's part of dQ's tiles (t = 1)
+            if constexpr (FIRST) {
+                const Span s(p.dQ + toff + (row0 + j0) * d);
+#pragma unroll
+                for (int x = 0; x < H::DT2; ++x) {
+                    const int e = 16 * (ig + x * NIG) + 4 * g;
+                    dqo[x] = s.loadf((jj * d + e) * 4, jj < jq && e < d);
+                }
+            }
+            fetch(j0 + C);  // past the last chunk: every load out of range, no traffic
+
+            // scores <Kbar[i], alpha_R[j]> and dR = Kbar . d alpha_L (+ Vbar . dY) (lane: i = 16t + 4g + q of row j)
+            f32x4 z[IPW], w[IPW];
+            Score<NP == 3> zs[IPW], ws[IPW];
+#pragma unroll
+            for (int c = 0; c < H::NC; ++c) {
+                const int r = (jt * 16 + c16) * LDX;
+                bf16x8 af[NP], df[3];
+                reads_stay();
+                read_chunk<NP>(As + r, H::PLR, c, g, af);
+                read_chunk<3>(Ds + r, H::PLR, c, g, df);
+#pragma unroll
+                for (int t = 0; t < IPW; ++t) {
+                    if constexpr (P.UL) {
+                        bf16x8 f[NP];
+                        read_chunk<NP>(US + ((ig * IPW + t) * 16 + c16) * LDX, H::PLU, c, g, f);
+                        zs[t].add(f, af);
+                        ws[t].add(f, df);
+                    } else {
+                        zs[t].add(kF[t][c], af);
+                        ws[t].add(kF[t][c], df);
+                    }
+                }
+                if constexpr (LAST) {
+                    reads_stay();
+                    read_chunk<3>(Ys + r, H::PLR, c, g, df);
+#pragma unroll
+                    for (int t = 0; t < IPW; ++t) ws[t].add(vF[t][c], df);
+                }
+            }
+#pragma unroll
+            for (int t = 0; t < IPW; ++t) z[t] = zs[t].value(), w[t] = ws[t].value();
+            // R = softmax_i and its pull-back.  The gradient of row j's logits needs d R + d c_L (log R + 1) up to
+            // a constant of the row: d c_L times the logits less their maximum stands in for the second term.
+            const bool live = jj < jb && (!LENS || kv > 0);  // a block of padding only has R = 0
+            const float cr = cRs[jj], dcl = dcLs[jj];
+            const float sc = live ? dm.s / cr : 0.f;
+            float mx = kMasked;
+#pragma unroll
+            for (int t = 0; t < IPW; ++t) {
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    if ((ig * IPW + t) * 16 + 4 * g + q < kv) mx = max_nan(mx, z[t][q]);
+                }
+            }
+            mx = wave_xor_max<32>(wave_xor_max<16>(mx)) * sc;
+            f32x4 e4[IPW];
+#pragma unroll
+            for (int t = 0; t < IPW; ++t) {
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    const float u = __builtin_fmaf(z[t][q], sc, -mx);
+                    e4[t][q] = (ig * IPW + t) * 16 + 4 * g + q < kv ? exp_nat(u) : 0.f;
+                    z[t][q] = u;
+                    w[t][q] = __builtin_fmaf(dcl, u, w[t][q]);
+                }
+            }
+            RowStat<NP == 3> st;
+            st.own(mx, e4, w);
+            if constexpr (NIG > 1) {
+                if (g == 0) stat[ig * C + jj] = f32x4{st.mx, st.sum, st.dot, st.rest};
+                __syncthreads();
+            }
+            st.template whole<NIG>(stat + jj, C, dcl, live);
+            const float off = dcl * st.mx;
+            __bf16 *rrow = Rs + jj * LDP, *zrow = Zs + jj * LDP;
+            float dzlog = 0.f;
+#pragma unroll
+            for (int t = 0; t < IPW; ++t) {
+                const int i = (ig * IPW + t) * 16 + 4 * g;
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    const float r = e4[t][q] * st.scale;  // masked keys: 0
+                    const float dz = r * st.centred(w[t][q] + off);
+                    dzlog = __builtin_fmaf(dz, z[t][q] + st.mx, dzlog);
+                    z[t][q] = r;
+                    w[t][q] = dz * sc;
+                }
+                store_factor(rrow + i, H::PLP, z[t]);
+                if constexpr (!P.MUX) store_factor(zrow + i, H::PLP, w[t]);
+            }
+            if constexpr (!FIRST) {
+                dzlog = lanegroup_sum(dzlog);
+                if (g == 0) part[ig * C + jj] = dzlog;
+            }
+            __syncthreads();
+            if constexpr (!FIRST) {  // zero for a block of padding only (read by l_bwd)
+                if (tid < jb) {
+                    float v = 0.f;
+#pragma unroll
+                    for (int x = 0; x < NIG; ++x) v += part[x * C + tid];
+                    p.dcR[coff + row0 + j0 + tid] = (!LENS || kv > 0) ? -v / cRs[tid] : 0.f;
+                }
+            }
+
+            // dKbar[i] += sum_j R[j][i] d alpha_L[j];  dVbar[i] += sum_j R[j][i] dY[j]
+            {
+                KJ rf[IPW][3];
+#pragma unroll
+                for (int t = 0; t < IPW; ++t) read_cols<H::KDJ, 3>(Rs, H::PLP, LDP, 0, (ig * IPW + t) * 16, lane, rf[t]);
+#pragma unroll
+                for (int x = 0; x < H::DTW; ++x) {
+                    KJ f[3];
+                    reads_stay();
+                    read_cols<H::KDJ, 3>(Ds, H::PLR, LDX, 0, (jt * H::DTW + x) * 16, lane, f);
+#pragma unroll
+                    for (int t = 0; t < IPW; ++t) mma_planes(f, rf[t], dK[t][x]);
+                    if constexpr (LAST) {
+                        reads_stay();
+                        read_cols<H::KDJ, 3>(Ys, H::PLR, LDX, 0, (jt * H::DTW + x) * 16, lane, f);
+#pragma unroll
+                        for (int t = 0; t < IPW; ++t) mma_planes(f, rf[t], dV[t][x]);
+                    }
+                }
+            }
+            if constexpr (P.MUX) {
+                __syncthreads();
+#pragma unroll
+                for (int t = 0; t < IPW; ++t) store_factor(zrow + (ig * IPW + t) * 16 + 4 * g, H::PLP, w[t]);
+                __syncthreads();
+            }
+            // dKbar[i] += sum_j dZs[j][i] alpha_R[j]
+            {
+                KJ zf[IPW][3];
+#pragma unroll
+                for (int t = 0; t < IPW; ++t) read_cols<H::KDJ, 3>(Zs, H::PLP, LDP, 0, (ig * IPW + t) * 16, lane, zf[t]);
+#pragma unroll
+                for (int x = 0; x < H::DTW; ++x) {
+                    KJ f[NP];
+                    reads_stay();
+                    read_cols<H::KDJ, NP>(As, H::PLR, LDX, 0, (jt * H::DTW + x) * 16, lane, f);
+#pragma unroll
+                    for (int t = 0; t < IPW; ++t) mma_planes(f, zf[t], dK[t][x]);
+                }
+            }
+            // d alpha_R[j] = sum_i dZs[j][i] Kbar[i]: to the workspace, or at step 1 into dq
+            f32x4 da[H::DT2];
+#pragma unroll
+            for (int x = 0; x < H::DT2; ++x) da[x] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int c = 0; c < H::NKI; ++c) {
+                KI r[3];
+                reads_stay();
+                read_row<H::KDI, 3>(zrow, H::PLP, H::KDI * c, g, r);
+#pragma unroll
+                for (int x = 0; x < H::DT2; ++x) {
+                    if (H::DT2 * NIG > H::NDT && ig + x * NIG >= H::NDT) continue;
+                    if constexpr (P.UL) {
+                        KI f[NP];
+                        read_cols<H::KDI, NP>(US, H::PLU, LDX, H::KDI * c, 16 * min(ig + x * NIG, H::NDT - 1), lane, f);
+                        mma_planes(f, r, da[x]);
+                    } else {
+                        mma_planes(kT[x][c], r, da[x]);
+                    }
+                }
+            }
+#pragma unroll
+            for (int x = 0; x < H::DT2; ++x) {
+                const int e = 16 * (ig + x * NIG) + 4 * g;
+                if constexpr (FIRST) {  // rows past the length: zero
+                    const f32x4 v = (!LENS || jj < jq) ? dqo[x] + da[x] : f32x4{0.f, 0.f, 0.f, 0.f};
+                    Span(p.dq + toff + (row0 + j0) * d).store<T>(v, (jj * d + e) * (int)sizeof(T), jj < (LENS ? jn : jq) && e < d);
+                } else {
+                    Span(p.daR + soff + (row0 + j0) * D).store<float>(da[x], (jj * D + e) * 4, jj < jb && e < d);
+                }
+            }
+            __syncthreads();  // the next chunk overwrites the rows and factors
+        }
+
+#pragma unroll
+        for (int t = 0; t < IPW; ++t) {
+            const int i = (ig * IPW + t) * 16 + c16;
+#pragma unroll
+            for (int x = 0; x < H::DTW; ++x) {
+                const int e = (jt * H::DTW + x) * 16 + 4 * g;
+                const int64_t u = toff + row0 * d;
+                const uint32_t o = i * d + e;
+                const bool in = i < (LENS && FIRST ? kn : kv) && e < d;  // at t = 1 rows past the length get zero
+                f32x4 v = dK[t][x];
+                if constexpr (!LAST) v += Span(p.dK + u).loadf(o * 4, i < kv && e < d);
+                if (LENS && i >= kv) v = f32x4{0.f, 0.f, 0.f, 0.f};
+                if constexpr (FIRST)
+                    Span(p.dk + u).store<T>(v, o * (uint32_t)sizeof(T), in);
+                else
+                    Span(p.dK + u).store<float>(v, o * 4, in);
+                if constexpr (LAST) {
+                    if (LENS && i >= kv) dV[t][x] = f32x4{0.f, 0.f, 0.f, 0.f};
+                    Span(p.dv + u).store<T>(dV[t][x], o * (uint32_t)sizeof(T), i < (LENS ? kn : kv) && e < d);
+                }
+            }
         }
     }
 };
 
 template <typename T, int S, int D, bool LAST, bool LENS>
-__global__ __launch_bounds__(64 * unit_waves(S)) void l_bwd(BwdBufs<T> p, BwdDims dm)
+__global__ __launch_bounds__((unit_threads<T, S, D, true, LAST>), (Shape<S, D, planes_of<T>, true, LAST>::TWO ? 4 : 1)) void l_bwd(BwdBufs<T> p, BwdDims dm)
 {
-    __shared__ __attribute__((aligned(16))) float lds[LBwd<T, S, D, LAST, LENS>::LDS_FLOATS];
-    LBwd<T, S, D, LAST, LENS>::run(p, dm, lds);
+    using U = LBwd<T, S, D, LAST, LENS>;
+    __shared__ __attribute__((aligned(16))) char lds[U::H::LDS_BYTES];
+    U::run(p, dm, lds);
 }
 
 template <typename T, int S, int D, bool FIRST, bool LAST, bool LENS>
-__global__ __launch_bounds__(64 * unit_waves(S)) void r_bwd(BwdBufs<T> p, BwdDims dm)
+__global__ __launch_bounds__((unit_threads<T, S, D, false, LAST>), (Shape<S, D, planes_of<T>, false, LAST>::TWO ? 4 : 1)) void r_bwd(BwdBufs<T> p, BwdDims dm)
 {
-    __shared__ __attribute__((aligned(16))) float lds[RBwd<T, S, D, FIRST, LAST, LENS>::LDS_FLOATS];
-    RBwd<T, S, D, FIRST, LAST, LENS>::run(p, dm, lds);
-}
-
-// The same kernels with registers bounded for two workgroups per CU.
-template <typename T, int S, int D, bool LAST, bool LENS>
-__global__ __launch_bounds__(64 * unit_waves(S)) __attribute__((amdgpu_waves_per_eu(2 * unit_waves(S) / 4))) void l_bwd2(
-    BwdBufs<T> p, BwdDims dm)
-{
-    __shared__ __attribute__((aligned(16))) float lds[LBwd<T, S, D, LAST, LENS>::LDS_FLOATS];
-    LBwd<T, S, D, LAST, LENS>::run(p, dm, lds);
-}
-
-template <typename T, int S, int D, bool FIRST, bool LAST, bool LENS>
-__global__ __launch_bounds__(64 * unit_waves(S)) __attribute__((amdgpu_waves_per_eu(2 * unit_waves(S) / 4))) void r_bwd2(
-    BwdBufs<T> p, BwdDims dm)
-{
-    __shared__ __attribute__((aligned(16))) float lds[RBwd<T, S, D, FIRST, LAST, LENS>::LDS_FLOATS];
-    RBwd<T, S, D, FIRST, LAST, LENS>::run(p, dm, lds);
+    using U = RBwd<T, S, D, FIRST, LAST, LENS>;
+    __shared__ __attribute__((aligned(16))) char lds[U::H::LDS_BYTES];
+    U::run(p, dm, lds);
 }
 
 }  // namespace bwd

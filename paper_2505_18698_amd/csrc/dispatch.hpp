@@ -28,12 +28,6 @@ template <typename T> ma::Bufs<T> typed(const CallBufs &B)
                        B.cR, B.cL, B.obj_part};
 }
 
-template <typename F> int launched(F &&f)
-{
-    f();
-    return MA_OK;
-}
-
 // Workgroups of `kern` (at `threads` threads) resident on one compute unit,
 // queried once per kernel.
 inline int resident_per_cu(const void *kern, int threads)
@@ -374,6 +368,42 @@ template <typename T> int run_call_impl(Launcher &L, const CallBufs &B, const Ca
                                obj, units, b);
         });
     });
+}
+
+// ---- gradient ----
+// The forward half-steps again, each step's states to buffers of their own,
+// then the reverse sweep.  States with rows of d elements; every (m, b, d) the
+// forward takes.
+template <typename T, int D> int run_bwd_d(Launcher &L, const BwdCallBufs &B, const CallDims &c)
+{
+    ma::HeadDims hd{c.m, c.b, c.n, c.d, c.s_log2e, 0};
+    hd.T = c.T;
+    hd.lens = B.lens;  // the recompute takes the same per-sequence lengths
+    hd.H = (int)c.H;
+    int rc;
+    for (int t = 1; t <= c.T; ++t) {
+        hd.t = t;
+        const bool first = t == 1, last = t == c.T;
+        const CallBufs r{B.q, B.k, B.v, nullptr,
+                         first ? nullptr : B.aR + (size_t)(t - 2) * B.st, B.aL + (size_t)(t - 1) * B.st, B.Y,
+                         first ? nullptr : B.cR + (size_t)(t - 2) * B.cst, B.cL + (size_t)(t - 1) * B.cst, nullptr,
+                         nullptr};
+        if ((rc = r_step<T, D>(L, r, hd, c.BH, c.num_cus, first, last)) != MA_OK) return rc;
+        if (last) break;
+        const CallBufs l{B.q, B.k, B.v, nullptr, B.aR + (size_t)(t - 1) * B.st, B.aL + (size_t)(t - 1) * B.st, B.Y,
+                         B.cR + (size_t)(t - 1) * B.cst, B.cL + (size_t)(t - 1) * B.cst, nullptr, nullptr};
+        if ((rc = l_step<T, D>(L, l, hd, c.BH, c.num_cus, false)) != MA_OK) return rc;
+    }
+    return bwd_sweep<T, D>(L, B, c);
+}
+
+template <typename T> int run_bwd_impl(Launcher &L, const BwdCallBufs &B, const CallDims &c)
+{
+    switch (tile_d(c.d)) {
+    case 64: return run_bwd_d<T, 64>(L, B, c);
+    case 96: return run_bwd_d<T, 96>(L, B, c);
+    default: return run_bwd_d<T, 128>(L, B, c);
+    }
 }
 
 }  // namespace ma_host

@@ -1,10 +1,13 @@
-// Launches of the gradient (monarch_attn_bwd): the forward half-steps again
-// with every step's states kept, then the reverse sweep of backward.hpp.
-// Instantiated once per element type in dispatch_{bf16,f16,f32}.hip.
+// Launches of the gradient's reverse sweep (backward.hpp).  Instantiated once
+// per element type and tile width in sweep_{bf16,f16,f32}_{64,96,128}.hip, so
+// that the kernels compile in parallel.
 #pragma once
 
+#include <cmath>
+#include <type_traits>
+
 #include "backward.hpp"
-#include "dispatch.hpp"
+#include "host_common.hpp"
 
 namespace ma_host {
 
@@ -12,28 +15,20 @@ namespace ma_host {
 template <typename T, int S, int D, bool LAST, bool LENS>
 int launch_l_bwd(Launcher &L, const ma::BwdBufs<T> &p, const ma::BwdDims &dm, int64_t BH)
 {
-    const dim3 grid((unsigned)(BH * dm.b)), block(ma::bwd::Geo<S, D, sizeof(T) == 2>::NTH);
+    const dim3 grid((unsigned)(BH * dm.b)), block(ma::bwd::unit_threads<T, S, D, true, LAST>);
     return L.run(kBwdL, [&] {
-        return launched([&] {
-            if constexpr (ma::bwd::two_per_cu(S, D, sizeof(T)))
-                hipLaunchKernelGGL((ma::bwd::l_bwd2<T, S, D, LAST, LENS>), grid, block, 0, L.stream, p, dm);
-            else
-                hipLaunchKernelGGL((ma::bwd::l_bwd<T, S, D, LAST, LENS>), grid, block, 0, L.stream, p, dm);
-        });
+        return launched(
+            [&] { hipLaunchKernelGGL((ma::bwd::l_bwd<T, S, D, LAST, LENS>), grid, block, 0, L.stream, p, dm); });
     });
 }
 
 template <typename T, int S, int D, bool FIRST, bool LAST, bool LENS>
 int launch_r_bwd(Launcher &L, const ma::BwdBufs<T> &p, const ma::BwdDims &dm, int64_t BH)
 {
-    const dim3 grid((unsigned)(BH * dm.m)), block(ma::bwd::Geo<S, D, sizeof(T) == 2>::NTH);
+    const dim3 grid((unsigned)(BH * dm.m)), block(ma::bwd::unit_threads<T, S, D, false, LAST>);
     return L.run(kBwdR, [&] {
-        return launched([&] {
-            if constexpr (ma::bwd::two_per_cu(S, D, sizeof(T)))
-                hipLaunchKernelGGL((ma::bwd::r_bwd2<T, S, D, FIRST, LAST, LENS>), grid, block, 0, L.stream, p, dm);
-            else
-                hipLaunchKernelGGL((ma::bwd::r_bwd<T, S, D, FIRST, LAST, LENS>), grid, block, 0, L.stream, p, dm);
-        });
+        return launched(
+            [&] { hipLaunchKernelGGL((ma::bwd::r_bwd<T, S, D, FIRST, LAST, LENS>), grid, block, 0, L.stream, p, dm); });
     });
 }
 
@@ -49,8 +44,8 @@ int l_bwd_step(Launcher &L, const ma::BwdBufs<T> &p, const ma::BwdDims &dm, int6
     case 32: return last ? launch_l_bwd<T, 32, D, true, LENS>(L, p, dm, BH) : launch_l_bwd<T, 32, D, false, LENS>(L, p, dm, BH);
     case 64: return last ? launch_l_bwd<T, 64, D, true, LENS>(L, p, dm, BH) : launch_l_bwd<T, 64, D, false, LENS>(L, p, dm, BH);
     default:
-        if constexpr (D == 128 && std::is_same<T, float>::value) {  // the forward takes no such fp32 shape
-            return fail(MA_EUNSUPPORTED, "fp32 128-row blocks need d <= 96");
+        if constexpr (D > 64 && std::is_same<T, float>::value) {  // the forward takes no such fp32 shape
+            return fail(MA_EUNSUPPORTED, "fp32 128-row blocks need d <= 64");
         } else {
             return last ? launch_l_bwd<T, 128, D, true, LENS>(L, p, dm, BH)
                         : launch_l_bwd<T, 128, D, false, LENS>(L, p, dm, BH);
@@ -76,8 +71,8 @@ int r_bwd_step(Launcher &L, const ma::BwdBufs<T> &p, const ma::BwdDims &dm, int6
     case 32: return r_bwd_tile<T, 32, D, LENS>(L, p, dm, BH, first, last);
     case 64: return r_bwd_tile<T, 64, D, LENS>(L, p, dm, BH, first, last);
     default:
-        if constexpr (D == 128 && std::is_same<T, float>::value) {  // the forward takes no such fp32 shape
-            return fail(MA_EUNSUPPORTED, "fp32 128-row blocks need d <= 96");
+        if constexpr (D > 64 && std::is_same<T, float>::value) {  // the forward takes no such fp32 shape
+            return fail(MA_EUNSUPPORTED, "fp32 128-row blocks need d <= 64");
         } else {
             return r_bwd_tile<T, 128, D, LENS>(L, p, dm, BH, first, last);
         }
@@ -110,41 +105,6 @@ template <typename T, int D, bool LENS> int bwd_sweep_impl(Launcher &L, const Bw
 template <typename T, int D> int bwd_sweep(Launcher &L, const BwdCallBufs &B, const CallDims &c)
 {
     return B.lens ? bwd_sweep_impl<T, D, true>(L, B, c) : bwd_sweep_impl<T, D, false>(L, B, c);
-}
-
-// The forward half-steps again, each step's states to buffers of their own,
-// then the reverse sweep.  States with rows of d elements; every (m, b, d) the
-// forward takes.
-template <typename T, int D> int run_bwd_d(Launcher &L, const BwdCallBufs &B, const CallDims &c)
-{
-    ma::HeadDims hd{c.m, c.b, c.n, c.d, c.s_log2e, 0};
-    hd.T = c.T;
-    hd.lens = B.lens;  // the recompute takes the same per-sequence lengths
-    hd.H = (int)c.H;
-    int rc;
-    for (int t = 1; t <= c.T; ++t) {
-        hd.t = t;
-        const bool first = t == 1, last = t == c.T;
-        const CallBufs r{B.q, B.k, B.v, nullptr,
-                         first ? nullptr : B.aR + (size_t)(t - 2) * B.st, B.aL + (size_t)(t - 1) * B.st, B.Y,
-                         first ? nullptr : B.cR + (size_t)(t - 2) * B.cst, B.cL + (size_t)(t - 1) * B.cst, nullptr,
-                         nullptr};
-        if ((rc = r_step<T, D>(L, r, hd, c.BH, c.num_cus, first, last)) != MA_OK) return rc;
-        if (last) break;
-        const CallBufs l{B.q, B.k, B.v, nullptr, B.aR + (size_t)(t - 1) * B.st, B.aL + (size_t)(t - 1) * B.st, B.Y,
-                         B.cR + (size_t)(t - 1) * B.cst, B.cL + (size_t)(t - 1) * B.cst, nullptr, nullptr};
-        if ((rc = l_step<T, D>(L, l, hd, c.BH, c.num_cus, false)) != MA_OK) return rc;
-    }
-    return bwd_sweep<T, D>(L, B, c);
-}
-
-template <typename T> int run_bwd_impl(Launcher &L, const BwdCallBufs &B, const CallDims &c)
-{
-    switch (tile_d(c.d)) {
-    case 64: return run_bwd_d<T, 64>(L, B, c);
-    case 96: return run_bwd_d<T, 96>(L, B, c);
-    default: return run_bwd_d<T, 128>(L, B, c);
-    }
 }
 
 }  // namespace ma_host

@@ -38,6 +38,12 @@ struct Timing {
 };
 extern Timing g_timing;
 
+template <typename F> int launched(F &&f)
+{
+    f();
+    return MA_OK;
+}
+
 struct Launcher {
     hipStream_t stream;
     bool timed;
@@ -144,6 +150,9 @@ struct BwdCallBufs {
     float *dQ, *dK, *daL, *dcL, *dY, *daR, *dcR;
     const int *lens = nullptr;  // [B] real rows per batch element (device), or null
 };
+
+// The gradient's reverse sweep for one element type and tile width (sweep_*.hip).
+template <typename T, int D> int bwd_sweep(Launcher &L, const BwdCallBufs &B, const CallDims &c);
 
 // Enqueue the gradient (forward recompute, then the reverse sweep) for one element type.
 template <typename T> int run_bwd(Launcher &L, const BwdCallBufs &B, const CallDims &c);

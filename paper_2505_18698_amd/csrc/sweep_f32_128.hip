@@ -1,0 +1,6 @@
+// The gradient's reverse sweep for element type float at tile width 128.
+#include "dispatch_bwd.hpp"
+
+namespace ma_host {
+template int bwd_sweep<float, 128>(Launcher &L, const BwdCallBufs &B, const CallDims &c);
+}  // namespace ma_host

@@ -1,0 +1,6 @@
+// The gradient's reverse sweep for element type float at tile width 96.
+#include "dispatch_bwd.hpp"
+
+namespace ma_host {
+template int bwd_sweep<float, 96>(Launcher &L, const BwdCallBufs &B, const CallDims &c);
+}  // namespace ma_host
