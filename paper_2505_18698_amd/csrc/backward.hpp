@@ -1022,7 +1022,9 @@ template <typename T, int S, int D, bool FIRST, bool LAST, bool LENS = false> st
                     if ((ig * IPW + t) * 16 + 4 * g + q < kv) mx = max_nan(mx, z[t][q]);
                 }
             }
-            mx = wave_xor_max<32>(wave_xor_max<16>(mx)) * sc;
+            // a wave of masked keys only: logits of zero here (their e is zero), no part in the row's maximum
+            const bool none = ig * IPW * 16 >= kv;
+            mx = none ? 0.f : wave_xor_max<32>(wave_xor_max<16>(mx)) * sc;
             f32x4 e4[IPW];
 #pragma unroll
             for (int t = 0; t < IPW; ++t) {
@@ -1037,10 +1039,11 @@ template <typename T, int S, int D, bool FIRST, bool LAST, bool LENS = false> st
             RowStat<NP == 3> st;
             st.own(mx, e4, w);
             if constexpr (NIG > 1) {
-                if (g == 0) stat[ig * C + jj] = f32x4{st.mx, st.sum, st.dot, st.rest};
+                if (g == 0) stat[ig * C + jj] = f32x4{none ? kMasked : st.mx, st.sum, st.dot, st.rest};
                 __syncthreads();
             }
             st.template whole<NIG>(stat + jj, C, dcl, live);
+            if (none) st.mx = st.scale = 0.f;
             const float off = dcl * st.mx;
             __bf16 *rrow = Rs + jj * LDP, *zrow = Zs + jj * LDP;
             float dzlog = 0.f;
