@@ -220,47 +220,6 @@ template <int NP> __device__ inline void read_chunk(const __bf16 *row, int plane
     for (int a = 0; a < NP; ++a) f[a] = *reinterpret_cast<const bf16x8 *>(row + a * plane + 32 * c + 8 * g);
 }
 
-// A uniform base address with 32-bit byte offsets.  A lane whose `ok` is false
-// takes an offset past the end: its load gives zero and its store is dropped,
-// by the hardware's range check.  No access sits under a branch, so the
-// compiler knows how many are in flight: a wait for the rows fetched a chunk
-// ago does not also wait for the stores issued since.
-struct Span {
-    __amdgpu_buffer_rsrc_t r;
-    static constexpr int kEnd = 0x7fffffff, kDefault = 0x00027000;  // raw, 32-bit data format
-    __device__ explicit Span(const void *base) : r(__builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(base), 0, kEnd, kDefault)) {}
-    __device__ static inline int at(uint32_t bytes, bool ok) { return ok ? (int)bytes : (int)0x80000000u; }
-    __device__ inline u32x4 load16(uint32_t bytes, bool ok) const
-    {
-        return __builtin_amdgcn_raw_buffer_load_b128(r, at(bytes, ok), 0, 0);
-    }
-    __device__ inline f32x4 loadf(uint32_t bytes, bool ok) const
-    {
-        const u32x4 v = load16(bytes, ok);
-        f32x4 f;
-        __builtin_memcpy(&f, &v, 16);
-        return f;
-    }
-    __device__ inline float load1(uint32_t bytes, bool ok) const
-    {
-        return __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(r, at(bytes, ok), 0, 0));
-    }
-    // four elements of E
-    template <typename E> __device__ inline void store(f32x4 v, uint32_t bytes, bool ok) const
-    {
-        if constexpr (sizeof(E) == 4) {
-            u32x4 u;
-            __builtin_memcpy(&u, &v, 16);
-            __builtin_amdgcn_raw_buffer_store_b128(u, r, at(bytes, ok), 0, 0);
-        } else {
-            E e[4] = {to_elem<E>(v[0]), to_elem<E>(v[1]), to_elem<E>(v[2]), to_elem<E>(v[3])};
-            u32x2 u;
-            __builtin_memcpy(&u, e, 8);
-            __builtin_amdgcn_raw_buffer_store_b64(u, r, at(bytes, ok), 0, 0);
-        }
-    }
-};
-
 // read_chunk from row `row` of E, d elements apart, in global memory (!ok: zero),
 // elements >= d zero (d a multiple of 16 bytes' worth).
 template <typename E, int NP> __device__ inline void load_chunk(const Span &s, int row, bool ok, int c, int g, int d, bf16x8 (&f)[NP])

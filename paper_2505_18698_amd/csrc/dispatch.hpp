@@ -17,34 +17,10 @@
 #include <unordered_map>
 
 #include "grouped.hpp"
-#include "host_common.hpp"
 #include "ma_kernels.hpp"
+#include "launch.hpp"
 
 namespace ma_host {
-
-template <typename T> ma::Bufs<T> typed(const CallBufs &B)
-{
-    return ma::Bufs<T>{(const T *)B.q, (const T *)B.k, (const T *)B.v, (T *)B.out, (T *)B.aR, (T *)B.aL, (T *)B.Y,
-                       B.cR, B.cL, B.obj_part};
-}
-
-// Workgroups of `kern` (at `threads` threads) resident on one compute unit,
-// queried once per kernel.
-inline int resident_per_cu(const void *kern, int threads)
-{
-    static std::mutex mu;
-    static std::unordered_map<const void *, int> cache;
-    std::lock_guard<std::mutex> lock(mu);
-    auto it = cache.find(kern);
-    if (it != cache.end()) return it->second;
-    int n = 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, kern, threads, 0) != hipSuccess || n < 1) {
-        (void)hipGetLastError();
-        n = 1;
-    }
-    cache.emplace(kern, n);
-    return n;
-}
 
 // Grid of a half-step launch: every unit once, at most one workgroup per
 // resident slot (the workgroups loop over units).
@@ -153,39 +129,6 @@ int run_half_steps(Launcher &L, const CallBufs &B, ma::HeadDims hd, const CallDi
         if ((rc = l_step<T, D>(L, B, hd, c.BH, c.num_cus, last)) != MA_OK) return rc;
     }
     return MA_OK;
-}
-
-// ---- one workgroup per head ----
-template <typename T, bool RGB, bool RGM, bool LENS = false>
-int launch_fused(Launcher &L, const CallBufs &B, ma::HeadDims hd, const CallDims &c)
-{
-    using U = ma::FusedHead<T, RGB, RGM, LENS>;
-    // one workgroup per compute unit (its LDS holds one), each looping over heads
-    const int64_t grid = c.BH < c.num_cus ? c.BH : c.num_cus;
-    hd.units = c.BH;
-    const ma::Bufs<T> p = typed<T>(B);
-    const int64_t BH = c.BH;
-    const int T_ = c.T;
-    return L.run(kFused, [&] {
-        return launched([&] {
-            hipLaunchKernelGGL((ma::monarch_fused_head<T, RGB, RGM, LENS>), dim3((unsigned)grid), dim3(64 * U::NW), 0,
-                               L.stream, p, hd, BH, T_);
-        });
-    });
-}
-
-template <typename T> int run_fused(Launcher &L, const CallBufs &B, ma::HeadDims hd, const CallDims &c)
-{
-    if constexpr (sizeof(T) != 2) {
-        return fail(MA_EUNSUPPORTED, "the fused kernel needs 16-bit elements");
-    } else {
-        if (hd.lens) return launch_fused<T, true, true, true>(L, B, hd, c);
-        const bool rgb = hd.b != 16 || hd.n != hd.m * hd.b, rgm = hd.m != 16;
-        if (rgb && rgm) return launch_fused<T, true, true>(L, B, hd, c);
-        if (rgb) return launch_fused<T, true, false>(L, B, hd, c);
-        if (rgm) return launch_fused<T, false, true>(L, B, hd, c);
-        return launch_fused<T, false, false>(L, B, hd, c);
-    }
 }
 
 // ---- one workgroup per (head, group of residue classes) ----
@@ -347,7 +290,10 @@ template <typename T> int run_call_impl(Launcher &L, const CallBufs &B, const Ca
                                            "no pre-padding and no objective");
     int rc;
     if (fam == kFamFused) {
-        rc = run_fused<T>(L, B, hd, c);
+        if constexpr (sizeof(T) == 2)
+            rc = run_fused<T>(L, B, hd, c);
+        else
+            rc = fail(MA_EUNSUPPORTED, "the fused kernel needs 16-bit elements");
     } else if (fam == kFamGroup) {
         rc = run_group<T>(L, B, hd, c);
     } else {

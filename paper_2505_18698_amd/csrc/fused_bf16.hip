@@ -1,0 +1,6 @@
+// The one-workgroup-per-head kernel for element type __bf16.
+#include "dispatch_fused.hpp"
+
+namespace ma_host {
+template int run_fused<__bf16>(Launcher &L, const CallBufs &B, ma::HeadDims hd, const CallDims &c);
+}  // namespace ma_host

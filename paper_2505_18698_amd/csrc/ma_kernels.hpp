@@ -171,6 +171,47 @@ template <typename T> __device__ inline void store4(T *dst, f32x4 v)
     }
 }
 
+// A uniform base address with 32-bit byte offsets.  A lane whose `ok` is false
+// takes an offset past the end: its load gives zero and its store is dropped,
+// by the hardware's range check.  No access sits under a branch, so the
+// compiler knows how many are in flight: a wait for the rows fetched a chunk
+// ago does not also wait for the stores issued since.
+struct Span {
+    __amdgpu_buffer_rsrc_t r;
+    static constexpr int kEnd = 0x7fffffff, kDefault = 0x00027000;  // raw, 32-bit data format
+    __device__ explicit Span(const void *base) : r(__builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(base), 0, kEnd, kDefault)) {}
+    __device__ static inline int at(uint32_t bytes, bool ok) { return ok ? (int)bytes : (int)0x80000000u; }
+    __device__ inline u32x4 load16(uint32_t bytes, bool ok) const
+    {
+        return __builtin_amdgcn_raw_buffer_load_b128(r, at(bytes, ok), 0, 0);
+    }
+    __device__ inline f32x4 loadf(uint32_t bytes, bool ok) const
+    {
+        const u32x4 v = load16(bytes, ok);
+        f32x4 f;
+        __builtin_memcpy(&f, &v, 16);
+        return f;
+    }
+    __device__ inline float load1(uint32_t bytes, bool ok) const
+    {
+        return __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(r, at(bytes, ok), 0, 0));
+    }
+    // four elements of E
+    template <typename E> __device__ inline void store(f32x4 v, uint32_t bytes, bool ok) const
+    {
+        if constexpr (sizeof(E) == 4) {
+            u32x4 u;
+            __builtin_memcpy(&u, &v, 16);
+            __builtin_amdgcn_raw_buffer_store_b128(u, r, at(bytes, ok), 0, 0);
+        } else {
+            E e[4] = {to_elem<E>(v[0]), to_elem<E>(v[1]), to_elem<E>(v[2]), to_elem<E>(v[3])};
+            u32x2 u;
+            __builtin_memcpy(&u, e, 8);
+            __builtin_amdgcn_raw_buffer_store_b64(u, r, at(bytes, ok), 0, 0);
+        }
+    }
+};
+
 // A [NR][D] tile split into 16-byte chunks over NTH threads (chunk idx =
 // tid + h * NTH is row idx / CPR), fetched from global memory into registers
 // and later staged into a row-major LDS tile.  Rows r >= `valid` are zero.
@@ -1241,306 +1282,6 @@ __global__ __launch_bounds__(64 * Split<NM / 16>::W) void monarch_apply(Bufs<T> 
     using U = Apply<T, NM, D, RAGGED, LENS>;
     __shared__ __attribute__((aligned(16))) char lds[U::LDS_BYTES];
     run_units<U, D>(p, hd, hd.b, lds);
-}
-
-// ---------------------------------------------------------------------------------------
-// Small heads (m, b <= 16, d = 64, 16-bit elements): the whole forward pass of
-// one head in one workgroup of 16 waves (the fully fused one-head-per-block
-// kernel for short sequences of Sec. 4, "Benchmarking"), with Q, K and every
-// state resident in LDS, so that only Q, K, V and O cross global memory.  LDS regions, each 16
-// blocks of 16 rows of LD elements, zero wherever there is no data:
-//   Qs[j][l] = Qbar[j][l] = Q[l*b + j]
-//   Ks[k][i] = Kbar[k][i] = K[k*b + i]; the last R half-step of block k
-//              overwrites its own block with Y[k][j]
-//   As[j][k] = alpha_L[j][k]; the L half-step of class j overwrites its own
-//              block with its probabilities P[l][k] (rows l >= m zero)
-//   Rs[k][j] = alpha_R[k][j]; the last R half-step of block k overwrites its
-//              own block with Vbar[k]
-// and c_R[k][j], c_L[j][k] in fp32.  In every half-step wave w does the unit
-// w (block k or class j; one wave per unit at 16 rows): it overwrites only its
-// own blocks, apart from the state it hands to the next half-step, and the
-// half-steps are separated by workgroup barriers.  A wave's LDS accesses take
-// effect in program order, so a unit may overwrite a block it has read.  The
-// arithmetic of a unit is that of RHalf / LHalf / Apply at 16 rows.
-// ---------------------------------------------------------------------------------------
-template <typename T, bool RGB, bool RGM, bool LENS = false> struct FusedHead {
-    static_assert(!LENS || (RGB && RGM), "per-sequence lengths need the masked softmaxes");
-    static_assert(sizeof(T) == 2, "16-bit elements only");
-    static constexpr int D = 64, NW = 16, LD = D + 8;  // 64 * NW threads (the launch bound below); rows + 16 bytes
-    // Blocks are BS elements apart: 16 rows plus 16 bytes, so that the 16
-    // lanes reading row r of 16 different blocks hit different LDS banks.
-    static constexpr int BS = 16 * LD + 8;
-    static constexpr int REGION = 16 * BS;  // elements
-    static constexpr int CS = 17;  // row stride (floats) of c_R and c_L: writes along a column avoid bank conflicts
-    static constexpr int LDS_BYTES = 4 * REGION * (int)sizeof(T) + 2 * 16 * CS * 4;
-
-    struct Ctx {
-        T *Qs, *Ks, *As, *Rs;
-        float *cRs, *cLs;  // c_R[k][j] at k*CS + j, c_L[j][k] at j*CS + k
-        int m, b, n, d, lane, g, c16;  // n: rows of a head in q, k, v, out; d <= D
-        int rev;                       // pre-padded: row x in memory at n - 1 - x (HeadDims::rev)
-        int nl, mk;        // with per-sequence lengths: real rows of the head being computed, live key blocks
-        float s_log2e;
-        int64_t bh;        // the head being computed
-        int steps;         // T, the step count
-        float *obj_part;   // objective shares [B*H][T][b], or nullptr
-    };
-
-    template <bool FIRST, bool FINAL>
-    __device__ static void r_unit(const Ctx &c, int k, const u32x4 *vpre)
-    {
-        const int j = c.c16;
-        const bool jv = j < c.b;
-        RowFrags<T, D> bf;  // row j of alpha_R[k]; at t = 1 that is Q[k*b + j] = Qs[j][k]
-        bf.load(FIRST ? c.Qs + j * BS + k * LD : c.Rs + k * BS + j * LD, c.g);
-        float rs = c.s_log2e;
-        if constexpr (!FIRST) {
-            if (jv) rs = c.s_log2e * fast_rcp(fmaxf(c.cRs[k * CS + j], kTiny));
-        }
-        T *Kk = c.Ks + k * BS;
-        const int kv = block_keys(c.b, LENS ? c.nl : c.n, k);  // keys >= kv: padding, masked (omega); none: R = 0
-        f32x4 sc;  // lane holds S'[i = 4g + qq][j]
-        gemm_scores_rt<T, D, 1>(Kk + c.c16 * LD, &bf, &sc, c.g);
-        const float nb = -tiles_max<1, RGB>(&sc, kv, c.g) * rs;
-        float sum = 0.f, t2 = 0.f;
-#pragma unroll
-        for (int qq = 0; qq < 4; ++qq) {
-            const float u = __builtin_fmaf(sc[qq], rs, nb);
-            float e = __builtin_amdgcn_exp2f(u);
-            if (RGB && 4 * c.g + qq >= kv) e = 0.f;
-            sum = qq == 0 ? e : sum + e;
-            t2 = qq == 0 ? e * u : __builtin_fmaf(e, u, t2);
-            sc[qq] = e;
-        }
-        sum = lanegroup_sum(sum);
-        t2 = lanegroup_sum(t2);
-        const bool live = !LENS || kv > 0;
-        const float inv = live ? fast_rcp(sum) : 0.f;
-        if (c.g == 0 && jv) c.cLs[j * CS + k] = live ? kLn2 * (t2 * inv - __builtin_amdgcn_logf(sum)) : 0.f;
-        static_assert(NormFirst<1, D>::value, "probabilities normalised before the products, as in RHalf");
-        sc *= inv;
-        ProbFrags<T, 1> pf;
-        pf.pack(&sc);
-        f32x4 out[D / 16];
-#pragma unroll
-        for (int vt = 0; vt < D / 16; ++vt) out[vt] = gemm_aggregate<T, 1>(Kk, LD, 16 * vt, pf, c.lane);
-        store_row_lds<T, D>(jv ? c.As + j * BS + k * LD : nullptr, out, c.lane);  // alpha_L[j][k]
-        if constexpr (FINAL) {
-            T *Vk = c.Rs + k * BS;  // alpha_R[k] has been read: stage Vbar[k] in its place
-#pragma unroll
-            for (int h = 0; h < 2; ++h)
-                *reinterpret_cast<u32x4 *>(Vk + ((c.lane >> 3) + 8 * h) * LD + (c.lane & 7) * 8) = vpre[h];
-#pragma unroll
-            for (int vt = 0; vt < D / 16; ++vt) out[vt] = gemm_aggregate<T, 1>(Vk, LD, 16 * vt, pf, c.lane);
-            store_row_lds<T, D>(jv ? Kk + j * LD : nullptr, out, c.lane);  // Y[k][j] over Kbar[k]
-        }
-    }
-
-    // Scores and softmax over k of class j, query row l = lane % 16 (lane
-    // holds k = 4g + qq); returns exp2 values and sets inv = 1 / row sum and
-    // lse = the row's logsumexp (natural units; 0 for tile rows l >= m).
-    __device__ static f32x4 l_softmax(const Ctx &c, int j, float &inv, float &lse)
-    {
-        RowFrags<T, D> bf;
-        bf.load(c.Qs + j * BS + c.c16 * LD, c.g);  // Qbar[j][l]
-        f32x4 acc;
-        gemm_scores_rt<T, D, 1>(c.As + j * BS + c.c16 * LD, &bf, &acc, c.g);
-        f32x4 sc;
-#pragma unroll
-        for (int qq = 0; qq < 4; ++qq) {
-            // entries k >= m hold no c_L (their LDS words are never written);
-            // the selects below leave them out of the maximum and the sum
-            const float bias = c.cLs[j * CS + 4 * c.g + qq] * kLog2e;
-            sc[qq] = __builtin_fmaf(acc[qq], c.s_log2e, -bias);
-        }
-        const int mk = LENS ? c.mk : c.m;  // blocks k >= mk: no real key
-        const float mx = tiles_max<1, RGM>(&sc, mk, c.g);
-        float sum = 0.f;
-#pragma unroll
-        for (int qq = 0; qq < 4; ++qq) {
-            float e = __builtin_amdgcn_exp2f(sc[qq] - mx);
-            if (RGM && 4 * c.g + qq >= mk) e = 0.f;
-            sum = qq == 0 ? e : sum + e;
-            sc[qq] = e;
-        }
-        sum = lanegroup_sum(sum);
-        const bool any = !LENS || mk > 0;  // a head without a real key has L = 0
-        inv = any ? fast_rcp(sum) : 0.f;
-        lse = (c.c16 < c.m && any) ? row_lse(mx, sum) : 0.f;
-        return sc;
-    }
-
-    // Objective share of class j after the L update of step t (as LHalf / Apply).
-    __device__ static void objective_share(const Ctx &c, int j, int t, float lse)
-    {
-        if (!c.obj_part) return;
-        const float part = rows16_sum(lse);
-        if (c.lane == 0) c.obj_part[(c.bh * c.steps + t - 1) * c.b + j] = part;
-    }
-
-    __device__ static void l_unit(const Ctx &c, int j, int t)
-    {
-        const int l = c.c16;
-        float inv, lse;
-        const f32x4 e = l_softmax(c, j, inv, lse);
-        objective_share(c, j, t, lse);
-        T *Aj = c.As + j * BS;  // alpha_L[j] has been read: P[l][k] in its place
-        const f32x4 pr = l < c.m ? e * inv : f32x4{0.f, 0.f, 0.f, 0.f};  // padded query rows carry no weight
-        store4<T>(Aj + l * LD + 4 * c.g, pr);
-        ProbFrags<T, 1> pf;  // B operand: P[l-slots][k = lane % 16]
-        pf.gather(Aj, LD, 0, c.lane);
-        const int k = c.c16;
-        const f32x4 cs = gemm_colsum<T, 1>(pf);  // c_R[k][j] = sum_l L[j][k][l]
-        if (c.g == 0 && k < c.m) c.cRs[k * CS + j] = cs[0];
-        f32x4 out[D / 16];
-#pragma unroll
-        for (int vt = 0; vt < D / 16; ++vt) out[vt] = gemm_aggregate<T, 1>(c.Qs + j * BS, LD, 16 * vt, pf, c.lane);
-        store_row_lds<T, D>(k < c.m ? c.Rs + k * BS + j * LD : nullptr, out, c.lane);  // alpha_R[k][j]
-    }
-
-    __device__ static void apply_unit(const Ctx &c, int j, T *out_h)
-    {
-        const int l = c.c16;
-        float inv, lse;
-        const f32x4 e = l_softmax(c, j, inv, lse) * inv;  // normalised first, as in Apply at 16 rows
-        objective_share(c, j, c.steps, lse);
-        ProbFrags<T, 1> pf;
-        pf.pack(&e);
-        f32x4 o[D / 16];  // O[l*b + j] = sum_k L[j][k][l] Y[k][j]; Y[k][j] is row k of Ks + j*LD at stride BS
-#pragma unroll
-        for (int vt = 0; vt < D / 16; ++vt) o[vt] = gemm_aggregate<T, 1>(c.Ks + j * LD, BS, 16 * vt, pf, c.lane);
-        const int row = l * c.b + j;  // rows nl..n-1 (batch padding) are written as zero
-        const int64_t mr = c.rev ? (int64_t)c.n - 1 - row : row;
-        store_row<T, D>(row < c.n ? out_h + mr * c.d : nullptr, o, (!LENS || row < c.nl) ? 1.0f : 0.f,
-                        c.lane, c.d);
-    }
-
-    static constexpr int PER = 2 * 256 * 8 / (64 * NW);  // 16-byte chunks of Qs and Ks per thread
-
-    // Issue the loads of head bh: Qbar and Kbar chunks (zero where there is no
-    // row) for the LDS regions, and Vbar[w] for wave w's last R half-step.
-    // Rows >= n (padding) and columns >= d are zero and never read.
-    __device__ static void load_head(const Bufs<T> &p, const HeadDims &hd, int64_t bh, int tid, u32x4 *raw, u32x4 *vb)
-    {
-        const int m = hd.m, b = hd.b, n = hd.n, d = hd.d;
-        const int64_t hoff = bh * (int64_t)n * d;
-        const T *qh = p.q + hoff, *kh = p.k + hoff, *vh = p.v + hoff;
-        // Row x of the problem is memory row x0 + sx * x (mrow); offsets within
-        // a head (at most 256 rows of 64 elements) are formed in 32 bits.
-        const int x0 = hd.rev ? n - 1 : 0, sx = hd.rev ? -1 : 1;
-#pragma unroll
-        for (int h = 0; h < PER; ++h) {
-            const int idx = tid + h * 64 * NW;
-            const int reg = idx >> 11, blk = (idx >> 7) & 15, r = (idx >> 3) & 15, col = (idx & 7) * 8;
-            raw[h] = u32x4{0u, 0u, 0u, 0u};
-            if (reg == 0 && blk < b && r < m && r * b + blk < n && col < d)
-                raw[h] = *reinterpret_cast<const u32x4 *>(qh + (x0 + sx * (r * b + blk)) * d + col);  // Qbar[blk][r]
-            if (reg == 1 && blk < m && r < b && blk * b + r < n && col < d)
-                raw[h] = *reinterpret_cast<const u32x4 *>(kh + (x0 + sx * (blk * b + r)) * d + col);  // Kbar[blk][r]
-        }
-        const int w = tid >> 6, lane = tid & 63;
-#pragma unroll
-        for (int h = 0; h < 2; ++h) {
-            const int r = (lane >> 3) + 8 * h, col = (lane & 7) * 8;
-            vb[h] = u32x4{0u, 0u, 0u, 0u};
-            if (w < m && r < b && w * b + r < n && col < d)
-                vb[h] = *reinterpret_cast<const u32x4 *>(vh + (x0 + sx * (w * b + r)) * d + col);
-        }
-    }
-
-    // 16-byte chunk idx of two consecutive regions: region idx >> 11, block
-    // (idx >> 7) & 15, row (idx >> 3) & 15.
-    __device__ static u32x4 *chunk(T *base, int idx)
-    {
-        return reinterpret_cast<u32x4 *>(base + (idx >> 11) * REGION + ((idx >> 7) & 15) * BS + ((idx >> 3) & 15) * LD +
-                                         (idx & 7) * 8);
-    }
-
-    // Heads blockIdx.x, blockIdx.x + gridDim.x, ... < BH.  The loads of the
-    // next head are issued as soon as the current one is in LDS and land
-    // while it is computed.  As and Rs are zeroed once: every head of a launch
-    // leaves zero in their padding rows (see the units).
-    __device__ static void run(const Bufs<T> &p, const HeadDims &hd, int64_t BH, int T_, char *lds)
-    {
-        Ctx c;
-        c.Qs = reinterpret_cast<T *>(lds);
-        c.Ks = c.Qs + REGION;
-        c.As = c.Ks + REGION;
-        c.Rs = c.As + REGION;
-        c.cRs = reinterpret_cast<float *>(c.Rs + REGION);
-        c.cLs = c.cRs + 16 * CS;
-        c.m = hd.m;
-        c.b = hd.b;
-        c.n = hd.n;
-        c.d = hd.d;
-        c.rev = hd.rev;
-        c.s_log2e = hd.s_log2e;
-        c.steps = T_;
-        c.obj_part = p.obj_part;
-        const int tid = threadIdx.x, w = tid >> 6;
-        c.lane = tid & 63;
-        c.g = c.lane >> 4;
-        c.c16 = c.lane & 15;
-        const int m = hd.m, b = hd.b;
-
-        u32x4 raw[PER], vcur[2], vnext[2];
-        int64_t bh = blockIdx.x;
-        load_head(p, hd, bh, tid, raw, vcur);
-        for (int idx = tid; idx < 2 * 256 * 8; idx += 64 * NW) *chunk(c.As, idx) = u32x4{0u, 0u, 0u, 0u};
-        for (; bh < BH; bh += gridDim.x) {
-            c.bh = bh;
-            if constexpr (LENS) {
-                // the loads of this head were issued with the static bound n:
-                // rows >= nl are zeroed here, on their way to LDS
-                c.nl = live_rows(hd, bh);
-                c.mk = live_blocks(m, b, c.nl);
-#pragma unroll
-                for (int h = 0; h < PER; ++h) {
-                    const int idx = tid + h * 64 * NW, blk = (idx >> 7) & 15, r = (idx >> 3) & 15;
-                    const int row = (idx >> 11) == 0 ? r * b + blk : blk * b + r;  // Qbar[blk][r] or Kbar[blk][r]
-                    *chunk(c.Qs, idx) = row < c.nl ? raw[h] : u32x4{0u, 0u, 0u, 0u};
-                }
-#pragma unroll
-                for (int h = 0; h < 2; ++h)
-                    if (w * b + (c.lane >> 3) + 8 * h >= c.nl) vcur[h] = u32x4{0u, 0u, 0u, 0u};  // Vbar[w]
-            } else {
-#pragma unroll
-                for (int h = 0; h < PER; ++h) *chunk(c.Qs, tid + h * 64 * NW) = raw[h];
-            }
-            __syncthreads();
-            if (bh + gridDim.x < BH) load_head(p, hd, bh + gridDim.x, tid, raw, vnext);
-
-            for (int t = 1; t <= T_; ++t) {
-                const bool first = t == 1, last = t == T_;
-                if (w < m) {
-                    if (first && last)
-                        r_unit<true, true>(c, w, vcur);
-                    else if (first)
-                        r_unit<true, false>(c, w, vcur);
-                    else if (last)
-                        r_unit<false, true>(c, w, vcur);
-                    else
-                        r_unit<false, false>(c, w, vcur);
-                }
-                __syncthreads();
-                if (last) break;
-                if (w < b) l_unit(c, w, t);
-                __syncthreads();
-            }
-            if (w < b) apply_unit(c, w, p.out + bh * (int64_t)c.n * c.d);
-            vcur[0] = vnext[0];
-            vcur[1] = vnext[1];
-            __syncthreads();  // the apply has read Qs, As and Ks
-        }
-    }
-};
-
-template <typename T, bool RGB, bool RGM, bool LENS>
-__global__ __launch_bounds__(1024) void monarch_fused_head(Bufs<T> p, HeadDims hd, int64_t BH, int T_)
-{
-    using U = FusedHead<T, RGB, RGM, LENS>;
-    __shared__ __attribute__((aligned(16))) char lds[U::LDS_BYTES];
-    U::run(p, hd, BH, T_, lds);
 }
 
 // f(M^(t); Q, K) of every (head, step): the objective shares summed over the

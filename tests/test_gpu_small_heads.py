@@ -1,0 +1,85 @@
+"""The one-workgroup-per-head kernel at every tile width (d up to 128): the
+automatic path gives the bits of the half-steps, on full and ragged heads,
+padded batches, pre-padding and with the objective, for fewer heads than the
+device holds at once and for more (a workgroup then takes several)."""
+import numpy as np
+import pytest
+
+import synth_inputs as si
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def ma():
+    import torch
+
+    assert torch.cuda.is_available(), "no GPU visible"
+    import paper_2505_18698_amd as lib
+
+    return lib
+
+
+def both(ma, call):
+    out = []
+    for path in (ma.PATH_HALF_STEPS, ma.PATH_AUTO):
+        prev = ma.monarch_attn_set_path(path)
+        try:
+            out.append(call())
+        finally:
+            ma.monarch_attn_set_path(prev)
+    return out
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f16"])
+@pytest.mark.parametrize("B,H,n,m,b,d,T", [
+    (1, 2, 256, 16, 16, 72, 3), (1, 3, 1, 1, 1, 128, 1), (2, 2, 15 * 14 - 13, 15, 14, 96, 2), (1, 2, 16, 1, 16, 104, 2),
+    (1, 2, 16, 16, 1, 80, 4), (3, 200, 9 * 7, 9, 7, 64, 2), (2, 280, 16 * 5 - 4, 16, 5, 128, 2), (1, 2, 40, 5, 8, 8, 2),
+])
+def test_bits_of_the_half_steps(ma, dtype, B, H, n, m, b, d, T):
+    import torch
+
+    td = {"bf16": torch.bfloat16, "f16": torch.float16}[dtype]
+    q, k, v = (torch.from_numpy(x).to(td).cuda() for x in si.random_qkv(B, H, n, d, dtype, seed=3, scale=1.5)[:3])
+    lens = torch.from_numpy(si.sequence_lengths(B, n, seed=4)).cuda()
+    lens[-1] = 0
+
+    def plain():
+        return ma.monarch_attn_fwd(q, k, v, torch.full_like(q, float("nan")), m, b, T)
+
+    def prepad():
+        return ma.monarch_attn_fwd_prepad(q, k, v, torch.full_like(q, float("nan")), m, b, T)
+
+    def varlen():
+        return ma.monarch_attn_fwd_varlen(q, k, v, torch.full_like(q, float("nan")), lens, m, b, T)
+
+    def objective():
+        obj = torch.full((B, H, T), float("nan"), device="cuda")
+        out, obj = ma.monarch_attn_fwd_objective(q, k, v, torch.full_like(q, float("nan")), obj, m, b, T)
+        return torch.cat((out.float().flatten(), obj.flatten()))
+
+    for call in (plain, prepad, varlen, objective):
+        one, two = both(ma, call)
+        torch.cuda.synchronize()
+        assert torch.isfinite(one.float()).all(), call.__name__
+        assert torch.equal(one, two), call.__name__
+
+
+def test_what_wide_small_heads_need_is_unchanged(ma):
+    """d > 64: forcing the one-workgroup-per-head path stays refused, and the
+    no-allocation call keeps its scratch limit."""
+    import torch
+
+    q = torch.zeros(1, 700, 256, 72, device="cuda", dtype=torch.bfloat16)
+    out = torch.empty_like(q)
+    prev = ma.monarch_attn_set_path(ma.PATH_FUSED)
+    try:
+        with pytest.raises(ma.MonarchAttnError):
+            ma.monarch_attn_fwd(q, q, q, out, 16, 16, 1)
+    finally:
+        ma.monarch_attn_set_path(prev)
+    assert ma.monarch_attn_workspace_bytes(1, 700, 256, 72, 16, 16, 1, ma.MA_BF16) > ma.NOALLOC_SCRATCH_BYTES
+    with pytest.raises(ma.MonarchAttnError):
+        ma.monarch_attn_fwd_noalloc(q, q, q, out, 16, 16, 1)
+    half = q[:, :300].contiguous()
+    ma.monarch_attn_fwd_noalloc(half, half, half, torch.empty_like(half), 16, 16, 1)
