@@ -470,7 +470,13 @@ def measure_backward(ma, torch, w, steps, warmup):
 
     # the recompute's launches follow the forward's plan (without the apply);
     # the sweep runs t = T .. 1 as (l_bwd, r_bwd) pairs
+    # (one launch where the one-workgroup-per-head kernel applies: Q, K, V in, the states out)
     fwd_plan = [p for p in launch_plan(w) if p[0] != "monarch_apply"]
+    if kinds[0] == "monarch_fused_head":
+        s = 2 if w.dtype in ("bf16", "f16") else 4
+        np_ = w.m * w.b
+        fwd_plan = [("monarch_fused_head", w.B * w.H * (3 * w.N * w.d * s + 2 * w.T * np_ * w.d * s + 4 * (2 * w.T - 1) * np_),
+                     sum(p[2] for p in fwd_plan))]
     nrec = len(fwd_plan)
     assert kinds[:nrec] == [p[0] for p in fwd_plan], (kinds, fwd_plan)
     kernels = []
@@ -489,8 +495,9 @@ def measure_backward(ma, torch, w, steps, warmup):
                         "TFLOP_s": round(nflops / (avg_ms * 1e-3) / 1e12, 2)})
     sweep = kernels[nrec:]
     dom = max(sweep, key=lambda x: x["avg_us"])
-    # the sweep's products are fp32 MFMA whatever the element type
-    roof = roofline_of(dom, "f32")
+    # the sweep's products run on the bf16 matrix instruction, fp32 operands as
+    # exact bf16 planes, whatever the element type
+    roof = roofline_of(dom, "bf16")
     roof["traffic"] = measured_traffic(f"{dom['kernel']}[t={dom['step']}]", w.name)
     return {"config": w.describe(), "value": round(w.B * w.H * w.N / (ms * 1e-3), 1), "unit": UNIT,
             "ms_per_call": round(ms, 6), "recompute_us": round(sum(x["avg_us"] for x in kernels[:nrec]), 3),
@@ -630,8 +637,8 @@ def quality(ma, torch, w, steps_list=(1, 2, 3)):
 # definitions and their launch configuration (the gradient's launches live
 # apart, so that changing them leaves the forward records valid).
 CSRC = os.path.join(ROOT, "paper_2505_18698_amd", "csrc")
-FWD_SOURCES = ("ma_kernels.hpp", "grouped.hpp", "dispatch.hpp")
-BWD_SOURCES = ("backward.hpp", "dispatch_bwd.hpp", "ma_kernels.hpp", "grouped.hpp", "dispatch.hpp")
+FWD_SOURCES = ("ma_kernels.hpp", "fused.hpp", "grouped.hpp", "dispatch.hpp")
+BWD_SOURCES = ("backward.hpp", "dispatch_bwd.hpp", "ma_kernels.hpp", "fused.hpp", "grouped.hpp", "dispatch.hpp")
 
 
 def kernel_sources_sha(kernel):

@@ -327,6 +327,16 @@ template <typename T, int D> int run_bwd_d(Launcher &L, const BwdCallBufs &B, co
     hd.lens = B.lens;  // the recompute takes the same per-sequence lengths
     hd.H = (int)c.H;
     int rc;
+    if constexpr (sizeof(T) == 2) {
+        // small heads: one launch of the one-workgroup-per-head kernel, the
+        // states to memory as it goes (384 heads of 15 x 14 rows, T = 2: 19.6 us
+        // against 27.5 us for three half-step launches)
+        if (c.m <= 16 && c.b <= 16) {
+            const CallBufs f{B.q, B.k, B.v, nullptr, B.aR, B.aL, B.Y, B.cR, B.cL, nullptr, nullptr, B.lens};
+            if ((rc = run_fused_states<T>(L, f, hd, c, (int64_t)(B.st / sizeof(T)), (int64_t)B.cst)) != MA_OK) return rc;
+            return bwd_sweep<T, D>(L, B, c);
+        }
+    }
     for (int t = 1; t <= c.T; ++t) {
         hd.t = t;
         const bool first = t == 1, last = t == c.T;

@@ -35,7 +35,17 @@
 
 namespace ma {
 
-template <typename T, int D, bool RGB, bool RGM, bool LENS = false> struct FusedHead {
+// Where the gradient's recompute keeps the states (FusedHead's KEEP): those of
+// step t `st` elements resp. `cst` floats after those of step t - 1, in the
+// layouts of Bufs (alpha_R and c_R from step 2 on).
+template <typename T> struct KeptStates {
+    T *aR, *aL, *Y;
+    float *cR, *cL;
+    int64_t st, cst;
+};
+
+// KEEP: the states go to memory as well, and O is not formed.
+template <typename T, int D, bool RGB, bool RGM, bool LENS = false, bool KEEP = false> struct FusedHead {
     static_assert(!LENS || (RGB && RGM), "per-sequence lengths need the masked softmaxes");
     static_assert(sizeof(T) == 2, "16-bit elements only");
     using M = Mma<T>;
@@ -62,6 +72,7 @@ template <typename T, int D, bool RGB, bool RGM, bool LENS = false> struct Fused
         int64_t bh;        // the head being computed
         int steps;         // T, the step count
         float *obj_part;   // objective shares [B*H][T][b], or nullptr
+        KeptStates<T> keep;  // of this head and step (KEEP)
     };
 
     // The 16 rows of block k of q, k or v in registers, 16-byte chunks in row
@@ -130,8 +141,11 @@ template <typename T, int D, bool RGB, bool RGM, bool LENS = false> struct Fused
         t2 = lanegroup_sum(t2);
         const bool live = !LENS || kv > 0;
         const float inv = live ? fast_rcp(sum) : 0.f;
-        if (c.g == 0 && jv && k < c.m)
-            c.cLs[j * CS + k] = live ? kLn2 * (t2 * inv - __builtin_amdgcn_logf(sum)) : 0.f;
+        if (c.g == 0 && jv && k < c.m) {
+            const float cl = live ? kLn2 * (t2 * inv - __builtin_amdgcn_logf(sum)) : 0.f;
+            c.cLs[j * CS + k] = cl;
+            if constexpr (KEEP) c.keep.cL[k * c.b + j] = cl;
+        }
         static_assert(NormFirst<1, D>::value, "probabilities normalised before the products, as in RHalf");
         sc *= inv;
         ProbFrags<T, 1> pf;
@@ -139,17 +153,20 @@ template <typename T, int D, bool RGB, bool RGM, bool LENS = false> struct Fused
         const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
         const bool on = jv && k < c.m;
         T *Kk = c.K + k * BS;
+        f32x4 o[NV];
 #pragma unroll
         for (int v = 0; v < NV; ++v) {
-            const f32x4 o = M::mma4(rows4<T>(Kk, LD, 0, 16 * v, c.lane), pf.f4, zero);
-            if (on) store4<T>(row + k * LD + 16 * v + 4 * c.g, o);  // alpha_L[j][k]
+            o[v] = M::mma4(rows4<T>(Kk, LD, 0, 16 * v, c.lane), pf.f4, zero);
+            if (on && !(KEEP && last)) store4<T>(row + k * LD + 16 * v + 4 * c.g, o[v]);  // alpha_L[j][k]
         }
+        if constexpr (KEEP) store_row<T, D>(on ? c.keep.aL + (j * c.m + k) * c.d : nullptr, o, 1.0f, c.lane, c.d);
         if (last) {  // Y[k][j] over Kbar[k] (blocks k >= m stay zero: they meet zero probabilities in the apply)
 #pragma unroll
             for (int v = 0; v < NV; ++v) {
-                const f32x4 o = M::mma4(un.vt[v], pf.f4, zero);
-                if (on) store4<T>(Kk + j * LD + 16 * v + 4 * c.g, o);
+                o[v] = M::mma4(un.vt[v], pf.f4, zero);
+                if (on && !KEEP) store4<T>(Kk + j * LD + 16 * v + 4 * c.g, o[v]);
             }
+            if constexpr (KEEP) store_row<T, D>(on ? c.keep.Y + (j * c.m + k) * c.d : nullptr, o, 1.0f, c.lane, c.d);
         }
     }
 
@@ -206,12 +223,17 @@ template <typename T, int D, bool RGB, bool RGM, bool LENS = false> struct Fused
         const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
         const f32x4 cs = gemm_colsum<T, 1>(pf);  // c_R[k][j] = sum_l L[j][k][l]
         const bool on = k < c.m && j < c.b;
-        if (c.g == 0 && on) c.cRs[k * CS + j] = cs[0];
+        if (c.g == 0 && on) {
+            c.cRs[k * CS + j] = cs[0];
+            if constexpr (KEEP) c.keep.cR[j * c.m + k] = cs[0];
+        }
+        f32x4 o[NV];
 #pragma unroll
         for (int v = 0; v < NV; ++v) {
-            const f32x4 o = M::mma4(un.qt[v], pf.f4, zero);
-            if (on) store4<T>(c.A + j * BS + k * LD + 16 * v + 4 * c.g, o);  // alpha_R[k][j]
+            o[v] = M::mma4(un.qt[v], pf.f4, zero);
+            if (on) store4<T>(c.A + j * BS + k * LD + 16 * v + 4 * c.g, o[v]);  // alpha_R[k][j]
         }
+        if constexpr (KEEP) store_row<T, D>(on ? c.keep.aR + (k * c.b + j) * c.d : nullptr, o, 1.0f, c.lane, c.d);
     }
 
     __device__ static void apply_unit(const Ctx &c, int j, const Unit &un, T *out_h)
@@ -233,7 +255,8 @@ template <typename T, int D, bool RGB, bool RGM, bool LENS = false> struct Fused
     }
 
     // Heads blockIdx.x, blockIdx.x + gridDim.x, ... < BH.
-    __device__ static void run(const Bufs<T> &p, const HeadDims &hd, int64_t BH, int T_, char *lds)
+    __device__ static void run(const Bufs<T> &p, const HeadDims &hd, int64_t BH, int T_, const KeptStates<T> &keep,
+                               char *lds)
     {
         Ctx c;
         c.A = reinterpret_cast<T *>(lds);
@@ -283,13 +306,18 @@ template <typename T, int D, bool RGB, bool RGM, bool LENS = false> struct Fused
             __syncthreads();  // the first half-step writes A
 
             for (int t = 1; t <= T_; ++t) {
+                if constexpr (KEEP) {
+                    const int64_t rows = bh * c.m * c.b, s0 = (t - 1) * keep.st + rows * c.d, c0 = (t - 1) * keep.cst + rows;
+                    c.keep = KeptStates<T>{keep.aR + s0, keep.aL + s0, keep.Y + rows * c.d, keep.cR + c0, keep.cL + c0, 0, 0};
+                }
                 r_unit(c, w, un, t == 1, t == T_);
+                if (KEEP && t == T_) break;
                 __syncthreads();
                 if (t == T_) break;
                 l_unit(c, w, t, un);
                 __syncthreads();
             }
-            apply_unit(c, w, un, p.out + hoff);
+            if constexpr (!KEEP) apply_unit(c, w, un, p.out + hoff);
             if (bh + gridDim.x < BH) __syncthreads();  // the next head overwrites A and K
         }
     }
@@ -300,7 +328,20 @@ __global__ __launch_bounds__(1024, D == 64 && !LENS ? 8 : 4) void monarch_fused_
 {
     using U = FusedHead<T, D, RGB, RGM, LENS>;
     __shared__ __attribute__((aligned(16))) char lds[U::LDS_BYTES];
-    U::run(p, hd, BH, T_, lds);
+    U::run(p, hd, BH, T_, KeptStates<T>{}, lds);
+}
+
+// The gradient's recompute of small heads: every step's states to memory, as
+// whole rows from the registers that hold them.  That takes 84 VGPRs at
+// D = 64, so one head a compute unit; holding it to 64 for two spills (384
+// heads of 15 x 14 rows, T = 2: 28 us against 19.6, and against 27.5 us on the
+// half-steps).
+template <typename T, int D, bool RGB, bool RGM, bool LENS>
+__global__ __launch_bounds__(1024, 4) void monarch_fused_states(Bufs<T> p, HeadDims hd, int64_t BH, int T_, KeptStates<T> keep)
+{
+    using U = FusedHead<T, D, RGB, RGM, LENS, true>;
+    __shared__ __attribute__((aligned(16))) char lds[U::LDS_BYTES];
+    U::run(p, hd, BH, T_, keep, lds);
 }
 
 }  // namespace ma

@@ -3,4 +3,6 @@
 
 namespace ma_host {
 template int run_fused<__bf16>(Launcher &L, const CallBufs &B, ma::HeadDims hd, const CallDims &c);
+template int run_fused_states<__bf16>(Launcher &L, const CallBufs &B, ma::HeadDims hd, const CallDims &c, int64_t st,
+                                  int64_t cst);
 }  // namespace ma_host

@@ -36,4 +36,9 @@ inline int resident_per_cu(const void *kern, int threads)
 // The forward pass of heads with m, b <= 16, one workgroup per head (fused_*.hip; 16-bit elements).
 template <typename T> int run_fused(Launcher &L, const CallBufs &B, ma::HeadDims hd, const CallDims &c);
 
+// The same heads' states of every step (the gradient's recompute), `st`
+// elements resp. `cst` floats from step to step.
+template <typename T>
+int run_fused_states(Launcher &L, const CallBufs &B, ma::HeadDims hd, const CallDims &c, int64_t st, int64_t cst);
+
 }  // namespace ma_host
