@@ -67,7 +67,7 @@
 // step-T R launch.
 #pragma once
 
-#include "ma_kernels.hpp"
+#include "planes.hpp"
 
 namespace ma {
 
@@ -100,192 +100,6 @@ __device__ inline int live_rows(const BwdDims &dm, int64_t bh)
     const int len = dm.lens[(int)bh / dm.H];
     return len < 0 ? 0 : len > dm.n ? dm.n : len;
 }
-
-typedef float f32x2 __attribute__((ext_vector_type(2)));
-typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
-
-// bf16 planes of an element type (split).
-template <typename T> constexpr int planes_of = std::is_same<T, float>::value ? 3 : std::is_same<T, __bf16>::value ? 1 : 2;
-
-// x[0..N) as the sum of NP bf16 planes, each the nearest bf16 value of what
-// the planes before it leave.
-template <int NP, int N, typename V> __device__ inline void split(const float *x, V (&p)[NP])
-{
-    float r[N];
-#pragma unroll
-    for (int i = 0; i < N; ++i) r[i] = x[i];
-#pragma unroll
-    for (int a = 0; a < NP; ++a) {
-#pragma unroll
-        for (int i = 0; i < N; i += 2) {  // two at a time: one conversion, and the halves of its result back as floats
-            const bf16x2 h = __builtin_convertvector((f32x2{r[i], r[i + 1]}), bf16x2);
-            p[a][i] = h[0];
-            p[a][i + 1] = h[1];
-            if (a + 1 < NP) {
-                uint32_t u;
-                __builtin_memcpy(&u, &h, 4);
-                r[i] -= __uint_as_float(u << 16);
-                r[i + 1] -= __uint_as_float(u & 0xffff0000u);
-            }
-        }
-    }
-}
-
-__device__ inline f32x4 mfma(bf16x8 a, bf16x8 b, f32x4 c) { return Mma<__bf16>::mma(a, b, c); }
-__device__ inline f32x4 mfma(bf16x4 a, bf16x4 b, f32x4 c) { return Mma<__bf16>::mma4(a, b, c); }
-
-// c += sum over the plane pairs, the smallest first.
-template <int NA, int NB, typename F> __device__ inline void mma_planes(const F (&a)[NA], const F (&b)[NB], f32x4 &c)
-{
-#pragma unroll
-    for (int s = 2; s >= 0; --s) {
-#pragma unroll
-        for (int i = 0; i < NA; ++i) {
-            const int j = s - i;
-            if (j >= 0 && j < NB) c = mfma(a[i], b[j], c);
-        }
-    }
-}
-
-// The scores and the factor's gradient, which the softmax and its pull-back
-// amplify: fp32 elements sum the leading planes' product (hi) apart from the
-// five small ones (lo), so that it takes one rounding a chunk and not six.
-template <bool TWO> struct Score {
-    f32x4 hi, lo;
-    __device__ Score() : hi{0.f, 0.f, 0.f, 0.f}, lo{0.f, 0.f, 0.f, 0.f} {}
-    template <int NA, int NB> __device__ inline void add(const bf16x8 (&a)[NA], const bf16x8 (&b)[NB])
-    {
-        if constexpr (TWO) {
-            hi = mfma(a[0], b[0], hi);
-#pragma unroll
-            for (int s = 2; s >= 1; --s) {
-#pragma unroll
-                for (int i = 0; i < NA; ++i) {
-                    const int j = s - i;
-                    if (j >= 0 && j < NB) lo = mfma(a[i], b[j], lo);
-                }
-            }
-        } else {
-            mma_planes(a, b, hi);
-        }
-    }
-    __device__ inline f32x4 value() const { return TWO ? hi + lo : hi; }
-};
-
-// Operand fragments of the products that contract over KD = 32 or 16 rows or
-// columns of a unit (KD = 16 only where the unit has no more).
-template <int KD> using Frag = typename std::conditional<KD == 32, bf16x8, bf16x4>::type;
-
-// Rows x0 .. x0 + KD - 1 (the contraction index), column c0 + lane % 16, of
-// every plane of a row-major LDS tile: slots 0..3 of lane group g are rows
-// 4g + q, slots 4..7 rows 16 + 4g + q.
-template <int KD, int NP>
-__device__ inline void read_cols(const __bf16 *X, int plane, int ld, int x0, int c0, int lane, Frag<KD> (&f)[NP])
-{
-#pragma unroll
-    for (int a = 0; a < NP; ++a) {
-        const bf16x4 lo = rows4<__bf16>(X + a * plane, ld, x0, c0, lane);
-        if constexpr (KD == 32) {
-            const bf16x4 hi = rows4<__bf16>(X + a * plane, ld, x0 + 16, c0, lane);
-            f[a] = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
-        } else {
-            f[a] = lo;
-        }
-    }
-}
-
-// Columns c0 .. c0 + KD - 1 (the contraction index) of row `row` of every
-// plane, in the slots of read_cols.
-template <int KD, int NP>
-__device__ inline void read_row(const __bf16 *row, int plane, int c0, int g, Frag<KD> (&f)[NP])
-{
-#pragma unroll
-    for (int a = 0; a < NP; ++a) {
-        const __bf16 *src = row + a * plane + c0 + 4 * g;
-        const bf16x4 lo = *reinterpret_cast<const bf16x4 *>(src);
-        if constexpr (KD == 32) {
-            const bf16x4 hi = *reinterpret_cast<const bf16x4 *>(src + 16);
-            f[a] = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
-        } else {
-            f[a] = lo;
-        }
-    }
-}
-
-// Elements 32c + 8g .. + 7 of a row of every plane of an LDS tile (products
-// that contract over the head dimension).
-template <int NP> __device__ inline void read_chunk(const __bf16 *row, int plane, int c, int g, bf16x8 (&f)[NP])
-{
-#pragma unroll
-    for (int a = 0; a < NP; ++a) f[a] = *reinterpret_cast<const bf16x8 *>(row + a * plane + 32 * c + 8 * g);
-}
-
-// read_chunk from row `row` of E, d elements apart, in global memory (!ok: zero),
-// elements >= d zero (d a multiple of 16 bytes' worth).
-template <typename E, int NP> __device__ inline void load_chunk(const Span &s, int row, bool ok, int c, int g, int d, bf16x8 (&f)[NP])
-{
-    constexpr int V = 16 / (int)sizeof(E);
-    E e[8];
-#pragma unroll
-    for (int v = 0; v < 8; v += V) {
-        const int col = 32 * c + 8 * g + v;
-        const u32x4 raw = s.load16((row * d + col) * (uint32_t)sizeof(E), ok && col < d);
-        __builtin_memcpy(e + v, &raw, 16);
-    }
-    if constexpr (NP == 1) {
-        __builtin_memcpy(&f[0], e, 16);
-    } else {
-        float x[8];
-#pragma unroll
-        for (int i = 0; i < 8; ++i) x[i] = static_cast<float>(e[i]);
-        split<NP, 8>(x, f);
-    }
-}
-
-// R rows of D elements of E from global memory into registers (fetch), and
-// from there into the NP planes of an LDS tile of row stride LD (stage), the
-// 16-byte chunks shared out over NTH threads.  Rows >= nr and columns >= nc
-// (a multiple of a chunk) are zero.
-template <typename E, int NP, int R, int D, int LD, int NTH> struct Rows {
-    static constexpr int V = 16 / (int)sizeof(E), CPR = D / V, ALL = R * CPR, CH = (ALL + NTH - 1) / NTH;
-    static constexpr int PLANE = R * LD;
-    u32x4 c[CH];
-
-    // Row r starts `step` elements after row r - 1 (offsets in 32 bits: within a head).
-    __device__ inline void fetch(const E *base, uint32_t step, int nr, int nc, int tid)
-    {
-        const Span s(base);
-#pragma unroll
-        for (int h = 0; h < CH; ++h) {
-            const int idx = tid + h * NTH, r = idx / CPR, col = (idx % CPR) * V;
-            c[h] = s.load16((r * step + col) * (uint32_t)sizeof(E), r < nr && col < nc);  // nr <= R
-        }
-    }
-
-    __device__ inline void stage(__bf16 *X, int tid) const
-    {
-#pragma unroll
-        for (int h = 0; h < CH; ++h) {
-            const int idx = tid + h * NTH, r = idx / CPR, col = (idx % CPR) * V;
-            if (ALL % NTH != 0 && idx >= ALL) break;
-            __bf16 *dst = X + r * LD + col;
-            if constexpr (NP == 1) {
-                *reinterpret_cast<u32x4 *>(dst) = c[h];
-            } else {
-                typedef __bf16 vec __attribute__((ext_vector_type(V)));
-                E e[V];
-                __builtin_memcpy(e, &c[h], 16);
-                float x[V];
-#pragma unroll
-                for (int i = 0; i < V; ++i) x[i] = static_cast<float>(e[i]);
-                vec p[NP];
-                split<NP, V>(x, p);
-#pragma unroll
-                for (int a = 0; a < NP; ++a) *reinterpret_cast<vec *>(dst + a * PLANE) = p[a];
-            }
-        }
-    }
-};
 
 // The four columns 16t + 4g + q that a lane holds of row `row` of a factor, as
 // three planes.
@@ -524,7 +338,7 @@ template <typename T, int S, int D, bool LAST, bool LENS = false> struct LBwd {
         float *sums = reinterpret_cast<float *>(stat + NIG * C);   // [NJT][S]
 
         // Qbar[j], dO of class j: rows step_l apart; rows k of alpha_L[j] and Y[j], d apart, or of d alpha_R'
-        const uint32_t step_l = (uint32_t)b * d;
+        const int step_l = b * d;
         const T *qb = p.q + toff + (int64_t)j * d, *gb = p.dout + toff + (int64_t)j * d;
         const T *ab = p.aL + xoff + (int64_t)j * m * d, *yb = p.Y + xoff + (int64_t)j * m * d;
         const float *xb = p.daR + soff + (int64_t)j * D;
@@ -537,7 +351,7 @@ template <typename T, int S, int D, bool LAST, bool LENS = false> struct LBwd {
         Rows<T, NP, S, D, LDX, NTH> ua;
         ua.fetch(ab, d, m, d, tid);
         Rows<float, 3, S, D, LDX, NTH> ux;
-        if constexpr (!LAST) ux.fetch(xb, (uint32_t)b * D, m, d, tid);
+        if constexpr (!LAST) ux.fetch(xb, b * D, m, d, tid);
         Rows<T, NP, C, D, LDX, NTH> qr, gr;
         qr.fetch(qb, step_l, min(max(ml, 0), C), d, tid);
         if constexpr (LAST) gr.fetch(gb, step_l, min(max(ml, 0), C), d, tid);
@@ -850,7 +664,7 @@ template <typename T, int S, int D, bool FIRST, bool LAST, bool LENS = false> st
         float *cRs = part + NIG * C, *dcLs = cRs + C;              // c_R, d c_L of the chunk's rows
 
         // rows j of alpha_R[k] (Q at t = 1), d apart; of d alpha_L and dY, step_j apart
-        const uint32_t step_j = (uint32_t)m * D;
+        const int step_j = m * D;
         const T *ab = FIRST ? p.q + toff + row0 * d : p.aR + xoff + row0 * d;
         const T *kb = p.k + toff + row0 * d, *vb = p.v + toff + row0 * d;
         const float *db = p.daL + soff + (int64_t)k * D, *yb = p.dY + soff + (int64_t)k * D;
