@@ -289,7 +289,7 @@ template <typename T> int run_call_impl(Launcher &L, const CallBufs &B, const Ca
                                          : "the grouped kernel needs bf16/fp16, d <= 64, m <= 64, b <= 32, no lengths, "
                                            "no pre-padding and no objective");
     int rc;
-    if (fam == kFamFused) {
+    if (fam == kFamFused || (path == kAuto && small_heads(dtype, c.m, c.b))) {
         if constexpr (sizeof(T) == 2)
             rc = run_fused<T>(L, B, hd, c);
         else
@@ -331,7 +331,7 @@ template <typename T, int D> int run_bwd_d(Launcher &L, const BwdCallBufs &B, co
         // small heads: one launch of the one-workgroup-per-head kernel, the
         // states to memory as it goes (384 heads of 15 x 14 rows, T = 2: 19.6 us
         // against 27.5 us for three half-step launches)
-        if (c.m <= 16 && c.b <= 16) {
+        if (small_heads(MA_BF16, c.m, c.b)) {
             const CallBufs f{B.q, B.k, B.v, nullptr, B.aR, B.aL, B.Y, B.cR, B.cL, nullptr, nullptr, B.lens};
             if ((rc = run_fused_states<T>(L, f, hd, c, (int64_t)(B.st / sizeof(T)), (int64_t)B.cst)) != MA_OK) return rc;
             return bwd_sweep<T, D>(L, B, c);

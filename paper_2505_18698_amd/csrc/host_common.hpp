@@ -113,10 +113,10 @@ inline bool grouped_applies(int32_t dtype, int64_t d, int64_t m, int64_t b, bool
     return (dtype == MA_BF16 || dtype == MA_F16) && d <= 64 && m <= 64 && b <= 32 && !lens && !obj;
 }
 
-// Heads of up to 16 blocks of up to 16 rows: the automatic path takes the
-// one-workgroup-per-head kernel at any d.  Forcing it (path 2) keeps to
-// fused_applies, and d > 64 to the workspace rules of the half-steps, which
-// ran these shapes before it did.
+// Heads of up to 16 blocks of up to 16 rows.  Where the automatic path gives
+// them to the half-steps (d > 64, beyond fused_applies), the half-steps'
+// launches are one of the one-workgroup-per-head kernel, which takes any d;
+// the workspace rules stay those of the half-steps.
 inline bool small_heads(int32_t dtype, int64_t m, int64_t b)
 {
     return (dtype == MA_BF16 || dtype == MA_F16) && m <= 16 && b <= 16;
@@ -136,7 +136,7 @@ inline int family_of(int path, int32_t dtype, int64_t d, int64_t m, int64_t b, b
     case kFusedHead: return fused_applies(dtype, d, m, b) ? kFamFused : kFamNone;
     case kGrouped: return grouped_applies(dtype, d, m, b, lens, obj) ? kFamGroup : kFamNone;
     default:
-        if (small_heads(dtype, m, b)) return kFamFused;
+        if (fused_applies(dtype, d, m, b)) return kFamFused;
         if (grouped_applies(dtype, d, m, b, lens, obj) && m <= 32) return kFamGroup;
         return kFamHalf;
     }

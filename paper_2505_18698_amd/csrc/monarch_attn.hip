@@ -281,8 +281,7 @@ int forward(const void *q, const void *k, const void *v, void *out, float *obj, 
     if ((rc = check_capture((hipStream_t)stream, capturing)) != MA_OK) return rc;
     std::unique_lock<std::mutex> ws_hold;  // the stream's workspace, held until the launches are enqueued
     const int fam = family_of(path, dtype, d, m, b, need_lens || prepad, need_obj);
-    // the other families keep their states in LDS (small heads with d > 64: see small_heads)
-    const bool states = fam == kFamHalf || (fam == kFamFused && d > 64);
+    const bool states = fam == kFamHalf;  // the other families keep their states in LDS
     const size_t obj_part_bytes = obj ? align_up((size_t)BH * T * b * sizeof(float)) : 0;
     if (states || obj) {
         const size_t state_ws = states ? workspace_bytes(BH, m * b, d, dtype) : 0;
