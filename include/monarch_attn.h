@@ -266,9 +266,9 @@ int monarch_attn_exact_fwd(const void *q, const void *k, const void *v, void *ou
  *                 T <= 32 for fp32 and T <= MONARCH_ATTN_MAX_T_16BIT_BWD
  *                 for bf16 and fp16 (else MA_EUNSUPPORTED).
  *
- * Runs the forward half-steps again, keeping the states of every step, then
- * one launch per half-step in reverse order; all of it on `stream`,
- * asynchronously.  The arithmetic of the reverse sweep is fp32 (the states
+ * Runs the forward half-steps again, keeping the states of every step (one
+ * launch for 16-bit heads with m, b <= 16), then one launch per half-step in
+ * reverse order; all of it on `stream`, asynchronously.  The arithmetic of the reverse sweep is fp32 (the states
  * of the recomputed forward pass are in the element type, as in
  * monarch_attn_fwd), and the result is deterministic (no atomics).
  * Workspace: monarch_attn_bwd_workspace_bytes(), in the same per-(device,
@@ -356,7 +356,9 @@ int monarch_attn_release_workspace(void);
  *      objective); any other call returns MA_EUNSUPPORTED.  Uses no
  *      workspace.
  * Automatic selection takes path 2 where it applies; else path 3 where it
- * applies with m <= 32; else path 1.  All paths compute the same operation with the same
+ * applies with m <= 32; else path 1, whose launches become the one kernel of
+ * path 2 for 16-bit heads with m, b <= 16 and d > 64 (path 1's workspace rules
+ * hold for them).  All paths compute the same operation with the same
  * per-unit arithmetic, and give the same bits.
  */
 int monarch_attn_set_path(int32_t path);

@@ -109,8 +109,6 @@ template <typename T, int D, bool RGB, bool RGM, bool LENS = false, bool KEEP = 
         for (int v = 0; v < NV; ++v) t[v] = rows4<T>(X, LD, 0, 16 * v, c.lane);
     }
 
-    // (A wave past m or b computes on zero rows and stores nothing.)
-
     // R half-step of block k (first: t = 1, c_R = 1; last: also Y).
     __device__ static void r_unit(const Ctx &c, int k, const Unit &un, bool first, bool last)
     {
@@ -141,7 +139,7 @@ template <typename T, int D, bool RGB, bool RGM, bool LENS = false, bool KEEP = 
         t2 = lanegroup_sum(t2);
         const bool live = !LENS || kv > 0;
         const float inv = live ? fast_rcp(sum) : 0.f;
-        if (c.g == 0 && jv && k < c.m) {
+        if (c.g == 0 && jv) {
             const float cl = live ? kLn2 * (t2 * inv - __builtin_amdgcn_logf(sum)) : 0.f;
             c.cLs[j * CS + k] = cl;
             if constexpr (KEEP) c.keep.cL[k * c.b + j] = cl;
@@ -151,7 +149,7 @@ template <typename T, int D, bool RGB, bool RGM, bool LENS = false, bool KEEP = 
         ProbFrags<T, 1> pf;
         pf.pack(&sc);
         const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
-        const bool on = jv && k < c.m;
+        const bool on = jv;
         T *Kk = c.K + k * BS;
         f32x4 o[NV];
 #pragma unroll
@@ -205,7 +203,7 @@ template <typename T, int D, bool RGB, bool RGM, bool LENS = false, bool KEEP = 
     {
         if (!c.obj_part) return;
         const float part = rows16_sum(lse);
-        if (c.lane == 0 && j < c.b) c.obj_part[(c.bh * c.steps + t - 1) * c.b + j] = part;
+        if (c.lane == 0) c.obj_part[(c.bh * c.steps + t - 1) * c.b + j] = part;
     }
 
     __device__ static void l_unit(const Ctx &c, int j, int t, const Unit &un)
@@ -222,7 +220,7 @@ template <typename T, int D, bool RGB, bool RGM, bool LENS = false, bool KEEP = 
         pf.gather(c.A + j * BS, LD, 0, c.lane);
         const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
         const f32x4 cs = gemm_colsum<T, 1>(pf);  // c_R[k][j] = sum_l L[j][k][l]
-        const bool on = k < c.m && j < c.b;
+        const bool on = k < c.m;
         if (c.g == 0 && on) {
             c.cRs[k * CS + j] = cs[0];
             if constexpr (KEEP) c.keep.cR[j * c.m + k] = cs[0];
@@ -250,7 +248,7 @@ template <typename T, int D, bool RGB, bool RGM, bool LENS = false, bool KEEP = 
         for (int v = 0; v < NV; ++v) o[v] = gemm_aggregate<T, 1>(c.K + j * LD, BS, 16 * v, pf, c.lane);
         const int row = c.c16 * c.b + j;  // rows nl..n-1 (batch padding) are written as zero
         const int64_t mr = c.rev ? (int64_t)c.n - 1 - row : row;
-        store_row<T, D>(j < c.b && row < c.n ? out_h + mr * c.d : nullptr, o, (!LENS || row < c.nl) ? 1.0f : 0.f,
+        store_row<T, D>(row < c.n ? out_h + mr * c.d : nullptr, o, (!LENS || row < c.nl) ? 1.0f : 0.f,
                         c.lane, c.d);
     }
 
@@ -310,21 +308,21 @@ template <typename T, int D, bool RGB, bool RGM, bool LENS = false, bool KEEP = 
                     const int64_t rows = bh * c.m * c.b, s0 = (t - 1) * keep.st + rows * c.d, c0 = (t - 1) * keep.cst + rows;
                     c.keep = KeptStates<T>{keep.aR + s0, keep.aL + s0, keep.Y + rows * c.d, keep.cR + c0, keep.cL + c0, 0, 0};
                 }
-                r_unit(c, w, un, t == 1, t == T_);
+                if (w < c.m) r_unit(c, w, un, t == 1, t == T_);
                 if (KEEP && t == T_) break;
                 __syncthreads();
                 if (t == T_) break;
-                l_unit(c, w, t, un);
+                if (w < c.b) l_unit(c, w, t, un);
                 __syncthreads();
             }
-            if constexpr (!KEEP) apply_unit(c, w, un, p.out + hoff);
+            if (!KEEP && w < c.b) apply_unit(c, w, un, p.out + hoff);
             if (bh + gridDim.x < BH) __syncthreads();  // the next head overwrites A and K
         }
     }
 };
 
 template <typename T, int D, bool RGB, bool RGM, bool LENS>
-__global__ __launch_bounds__(1024, D == 64 && !LENS ? 8 : 4) void monarch_fused_head(Bufs<T> p, HeadDims hd, int64_t BH, int T_)
+__global__ __launch_bounds__(1024, D == 64 ? 8 : 4) void monarch_fused_head(Bufs<T> p, HeadDims hd, int64_t BH, int T_)
 {
     using U = FusedHead<T, D, RGB, RGM, LENS>;
     __shared__ __attribute__((aligned(16))) char lds[U::LDS_BYTES];
