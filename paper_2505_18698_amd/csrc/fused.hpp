@@ -321,8 +321,10 @@ template <typename T, int D, bool RGB, bool RGM, bool LENS = false, bool KEEP = 
     }
 };
 
-template <typename T, int D, bool RGB, bool RGM, bool LENS>
-__global__ __launch_bounds__(1024, D == 64 ? 8 : 4) void monarch_fused_head(Bufs<T> p, HeadDims hd, int64_t BH, int T_)
+// TWO: registers for two heads a compute unit (64 VGPRs, a few spilled in the
+// masked forms), for calls with more heads than compute units.
+template <typename T, int D, bool RGB, bool RGM, bool LENS, bool TWO>
+__global__ __launch_bounds__(1024, TWO ? 8 : 4) void monarch_fused_head(Bufs<T> p, HeadDims hd, int64_t BH, int T_)
 {
     using U = FusedHead<T, D, RGB, RGM, LENS>;
     __shared__ __attribute__((aligned(16))) char lds[U::LDS_BYTES];
