@@ -29,14 +29,10 @@
 //       d alpha_R is added to dQ (alpha_R = the rows of Q) and c_R is constant.
 //
 // Products.  The sweep's arithmetic is fp32: gradients, factors and
-// accumulators are fp32, and every operand keeps all its bits.  An fp32 value
-// is the exact sum of three bf16 values (its leading 8 bits, the next 8, the
-// rest: `split`), an fp16 value of two, a bf16 value of one; these are the
-// operand's planes.  A product runs on the bf16 matrix instruction (16x16x32:
-// 16 times the fp32 one's rate) once for every pair of planes p, q with
-// p + q <= 2, accumulating in fp32: 1 to 6 instructions a tile and chunk.  The
-// pairs left out are below 2^-26 of the product, less than the rounding of one
-// fp32 multiply.
+// accumulators are fp32, and a product runs on the bf16 matrix instruction
+// over its operands' planes (planes.hpp, which states their range), 1 to 6
+// instructions a tile and chunk.  An infinite dO gives infinities in dV, as
+// fp32 products do; in the gradients of the factors they cancel to NaN.
 //
 // A unit (a block k of r_bwd, a class j of l_bwd) is one workgroup.  Its
 // columns (keys i, or key blocks k) are shared out over the waves in groups of
@@ -103,11 +99,11 @@ __device__ inline int live_rows(const BwdDims &dm, int64_t bh)
 
 // The four columns 16t + 4g + q that a lane holds of row `row` of a factor, as
 // three planes.
-__device__ inline void store_factor(__bf16 *row, int plane, f32x4 x)
+template <Reach R> __device__ inline void store_factor(__bf16 *row, int plane, f32x4 x)
 {
     const float v[4] = {x[0], x[1], x[2], x[3]};
     bf16x4 p[3];
-    split<3, 4>(v, p);
+    split<3, 4, R>(v, p);
 #pragma unroll
     for (int a = 0; a < 3; ++a) *reinterpret_cast<bf16x4 *>(row + a * plane) = p[a];
 }
@@ -297,6 +293,17 @@ template <int S, int D, int NP, bool LK, bool LAST> struct Shape {
     static constexpr int DT2 = dt2(0);
     static constexpr int PLU = S * LDX, PLR = C * LDX, PLP = C * LDP;  // plane strides
     static constexpr int LDS_BYTES = lds_bytes(P);
+    // Waves a SIMD that the registers are held to, where it takes no spills (the
+    // compiler otherwise ends one or two registers over the step).
+    static constexpr int waves()
+    {
+        if (TWO) return 4;
+        if (D == 64 && NP == 1 && LK && LAST && S <= 32) return S == 16 ? 3 : 4;
+        if (D == 64 && NP == 1 && !LK && !LAST && S == 64) return 3;
+        if (S == 16 && (D <= 96 || (NP == 1 && !LK && !LAST))) return 2;
+        return 1;
+    }
+    static constexpr int WAVES = waves();
 };
 
 // Waves of a unit's workgroup (the launch bound).
@@ -352,7 +359,8 @@ template <typename T, int S, int D, bool LAST, bool LENS = false> struct LBwd {
         ua.fetch(ab, d, m, d, tid);
         Rows<float, 3, S, D, LDX, NTH> ux;
         if constexpr (!LAST) ux.fetch(xb, b * D, m, d, tid);
-        Rows<T, NP, C, D, LDX, NTH> qr, gr;
+        Rows<T, NP, C, D, LDX, NTH> qr;
+        Rows<T, NP, C, D, LDX, NTH, Reach::kInf> gr;
         qr.fetch(qb, step_l, min(max(ml, 0), C), d, tid);
         if constexpr (LAST) gr.fetch(gb, step_l, min(max(ml, 0), C), d, tid);
         f32x4 cl[IPW], dcr[IPW];  // c_L[j][k], d c_R'[k][j]
@@ -513,8 +521,8 @@ template <typename T, int S, int D, bool LAST, bool LENS = false> struct LBwd {
                     w[t][q] = dm.s * z[t][q] * st.centred(w[t][q]);  // dW
                 }
                 dcl[t] += w[t];
-                store_factor(lrow + k, H::PLP, z[t]);
-                if constexpr (!P.MUX) store_factor(wrow + k, H::PLP, w[t]);
+                store_factor<Reach::kUnit>(lrow + k, H::PLP, z[t]);
+                if constexpr (!P.MUX) store_factor<Reach::kFinite>(wrow + k, H::PLP, w[t]);
             }
             __syncthreads();
 
@@ -532,7 +540,7 @@ template <typename T, int S, int D, bool LAST, bool LENS = false> struct LBwd {
                     reads_stay();
                     read_cols<H::KDJ, NP>(Gs, H::PLR, LDX, 0, (jt * H::DTW + x) * 16, lane, f);
 #pragma unroll
-                    for (int t = 0; t < IPW; ++t) mma_planes(f, lf[t], dY[t][x]);
+                    for (int t = 0; t < IPW; ++t) mma_planes_inf(f, lf[t], dY[t][x]);
                 }
             } else {
                 // dQbar[l] += sum_k L[l][k] d alpha_R'[k]
@@ -557,7 +565,7 @@ template <typename T, int S, int D, bool LAST, bool LENS = false> struct LBwd {
             if constexpr (P.MUX) {
                 __syncthreads();
 #pragma unroll
-                for (int t = 0; t < IPW; ++t) store_factor(wrow + (ig * IPW + t) * 16 + 4 * g, H::PLP, w[t]);
+                for (int t = 0; t < IPW; ++t) store_factor<Reach::kFinite>(wrow + (ig * IPW + t) * 16 + 4 * g, H::PLP, w[t]);
                 __syncthreads();
             }
             // d alpha_L[k] += sum_l dW[l][k] Qbar[l]
@@ -676,7 +684,8 @@ template <typename T, int S, int D, bool FIRST, bool LAST, bool LENS = false> st
         Rows<T, NP, S, D, LDX, NTH> uk;
         uk.fetch(kb, d, max(kv, 0), d, tid);
         Rows<T, NP, C, D, LDX, NTH> ar;
-        Rows<float, 3, C, D, LDX, NTH> dr, yr;
+        Rows<float, 3, C, D, LDX, NTH> dr;
+        Rows<float, 3, C, D, LDX, NTH, Reach::kInf> yr;
         float crr = 1.f, dclr = 0.f;
         auto fetch = [&](int j0) {
             const int jb = min(b - j0, C);
@@ -831,8 +840,8 @@ template <typename T, int S, int D, bool FIRST, bool LAST, bool LENS = false> st
                     z[t][q] = r;
                     w[t][q] = dz * sc;
                 }
-                store_factor(rrow + i, H::PLP, z[t]);
-                if constexpr (!P.MUX) store_factor(zrow + i, H::PLP, w[t]);
+                store_factor<Reach::kUnit>(rrow + i, H::PLP, z[t]);
+                if constexpr (!P.MUX) store_factor<Reach::kFinite>(zrow + i, H::PLP, w[t]);
             }
             if constexpr (!FIRST) {
                 dzlog = lanegroup_sum(dzlog);
@@ -871,7 +880,7 @@ template <typename T, int S, int D, bool FIRST, bool LAST, bool LENS = false> st
             if constexpr (P.MUX) {
                 __syncthreads();
 #pragma unroll
-                for (int t = 0; t < IPW; ++t) store_factor(zrow + (ig * IPW + t) * 16 + 4 * g, H::PLP, w[t]);
+                for (int t = 0; t < IPW; ++t) store_factor<Reach::kFinite>(zrow + (ig * IPW + t) * 16 + 4 * g, H::PLP, w[t]);
                 __syncthreads();
             }
             // dKbar[i] += sum_j dZs[j][i] alpha_R[j]
@@ -948,7 +957,7 @@ template <typename T, int S, int D, bool FIRST, bool LAST, bool LENS = false> st
 };
 
 template <typename T, int S, int D, bool LAST, bool LENS>
-__global__ __launch_bounds__((unit_threads<T, S, D, true, LAST>), (Shape<S, D, planes_of<T>, true, LAST>::TWO ? 4 : 1)) void l_bwd(BwdBufs<T> p, BwdDims dm)
+__global__ __launch_bounds__((unit_threads<T, S, D, true, LAST>), (Shape<S, D, planes_of<T>, true, LAST>::WAVES)) void l_bwd(BwdBufs<T> p, BwdDims dm)
 {
     using U = LBwd<T, S, D, LAST, LENS>;
     __shared__ __attribute__((aligned(16))) char lds[U::H::LDS_BYTES];
@@ -956,7 +965,7 @@ __global__ __launch_bounds__((unit_threads<T, S, D, true, LAST>), (Shape<S, D, p
 }
 
 template <typename T, int S, int D, bool FIRST, bool LAST, bool LENS>
-__global__ __launch_bounds__((unit_threads<T, S, D, false, LAST>), (Shape<S, D, planes_of<T>, false, LAST>::TWO ? 4 : 1)) void r_bwd(BwdBufs<T> p, BwdDims dm)
+__global__ __launch_bounds__((unit_threads<T, S, D, false, LAST>), (Shape<S, D, planes_of<T>, false, LAST>::WAVES)) void r_bwd(BwdBufs<T> p, BwdDims dm)
 {
     using U = RBwd<T, S, D, FIRST, LAST, LENS>;
     __shared__ __attribute__((aligned(16))) char lds[U::H::LDS_BYTES];

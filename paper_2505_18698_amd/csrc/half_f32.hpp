@@ -37,7 +37,7 @@ template <int D> struct RowRaw {
         __builtin_memcpy(x, &v[c][0], 32);
 #pragma unroll
         for (int i = 0; i < 8; ++i) x[i] = drop ? 0.f : x[i];
-        split<3, 8>(x, f);
+        split<3, 8, Reach::kFinite>(x, f);
     }
 };
 
@@ -53,7 +53,7 @@ template <int NT> struct Probs32 {
             float x[KD / 4];
 #pragma unroll
             for (int i = 0; i < KD / 4; ++i) x[i] = p[(KD / 16) * c + i / 4][i % 4];
-            split<3, KD / 4>(x, f[c]);
+            split<3, KD / 4, Reach::kUnit>(x, f[c]);
         }
     }
     // out[r][col] = sum_x X[x][c0 + r] p[x][col]: X's planes in LDS, rows the contraction index
@@ -93,9 +93,11 @@ template <int NB, int D, bool FIRST, bool FINAL, bool RAGGED, bool LENS = false>
     static constexpr int NT = NB / 16, W = NT, NTH = 64 * W, LD = D + 16, PLANE = NB * LD;
     static constexpr int LDS_BYTES = 3 * PLANE * 2;  // Kbar[k], then (FINAL) Vbar[k] in its place
     using Tile = Rows<float, 3, NB, D, LD, NTH>;
+    using VTile = Rows<float, 3, NB, D, LD, NTH, Reach::kInf>;
 
     struct Regs {
-        Tile kt, vt;
+        Tile kt;
+        VTile vt;
         RowRaw<D> row;  // row j of alpha_R[k] (of Q when FIRST)
         float cr;
         int nl, row0;   // real rows of the head, first key row k*b (LENS)
@@ -122,7 +124,7 @@ template <int NB, int D, bool FIRST, bool FINAL, bool RAGGED, bool LENS = false>
         if constexpr (FINAL) gr.vt.fetch(p.v + toff, step, kv, d, tid, first);
     }
 
-    __device__ static void clear(Tile &t, int valid, int tid)
+    template <typename U> __device__ static void clear(U &t, int valid, int tid)
     {
 #pragma unroll
         for (int h = 0; h < Tile::CH; ++h)
@@ -194,6 +196,7 @@ template <int NB, int D, bool FIRST, bool FINAL, bool RAGGED, bool LENS = false>
 template <int NM, int D, bool RAGGED, bool LENS> struct LBase32 {
     static constexpr int NT = NM / 16, W = NT, NTH = 64 * W, LD = D + 16, PLANE = NM * LD;
     using Tile = Rows<float, 3, NM, D, LD, NTH>;
+    using YTile = Rows<float, 3, NM, D, LD, NTH, Reach::kInf>;
 
     // Z (log2 units) of the wave's rows: lane holds k = 16t + 4g + qq of row l = 16 wave + c16.
     __device__ static void logits(const HeadDims &hd, const __bf16 *As, const float *cLs, const bf16x8 (&bf)[D / 32][3],
@@ -371,7 +374,8 @@ template <int NM, int D, bool RAGGED, bool LENS = false> struct Apply32 : LBase3
     static constexpr int T_BYTES = 3 * PLANE * 2, LDS_BYTES = 2 * T_BYTES + NM * 4 + W * 4;  // alpha_L[j], Y[j]
 
     struct Regs {
-        Tile at, yt;
+        Tile at;
+        typename B::YTile yt;
         float cl;
         RowRaw<D> row;  // row l of Qbar[j]
         int nl;

@@ -1,9 +1,17 @@
-// fp32 products on the bf16 matrix instruction.  An fp32 value is the exact sum
-// of three bf16 values (its planes: the leading 8 bits, the next 8, the rest),
-// an fp16 value of two, a bf16 value of one.  A product runs on the 16x16x32
+// fp32 products on the bf16 matrix instruction.  An fp32 value is the sum of
+// three bf16 values (its planes: the leading 8 bits, the next 8, the rest), an
+// fp16 value of two, a bf16 value of one.  A product runs on the 16x16x32
 // instruction (16 times the rate of the fp32 16x16x4 one) once for every pair
-// of planes p, q with p + q <= 2, accumulating in fp32; the pairs left out are
-// below 2^-26 of it, less than the rounding of one fp32 multiply.
+// of planes p, q with p + q <= 2, accumulating in fp32.  The pairs left out
+// are at most 2^-24 of it, the rounding of one fp32 multiply, and below 2^-26
+// for 97% of uniform operands.
+//
+// Range.  The sum is exact for finite values from 2^-110 up.  The instruction
+// takes bf16 values below 2^-126 as zero, so a smaller operand keeps 16 bits
+// (from 2^-117 up) or 8: a gradient that is 2^-115 as a whole has a relative
+// error of 3e-3, one of 2^-100 that of any other.  Sums of products may round to
+// an infinity where they come within 2^-16 of the end of fp32's range.  An
+// infinity is not a sum of planes; Reach::kInf says what stands for it.
 #pragma once
 
 #include "tiles.hpp"
@@ -16,18 +24,38 @@ typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 // bf16 planes of an element type (split).
 template <typename T> constexpr int planes_of = std::is_same<T, float>::value ? 3 : std::is_same<T, __bf16>::value ? 1 : 2;
 
+// Which values the planes of an operand stand for.
+enum class Reach {
+    kUnit,    // factors of a softmax: nothing near the end of fp32's range
+    kFinite,  // every finite value: one more instruction an element, as those beyond
+              // 3.396e38 would round to an infinite leading plane; an infinity gives NaN
+    kInf,     // infinities too.  In three planes an infinity is a finite leading plane, a
+              // finite second one, and itself: the last plane meets only the other
+              // operand's leading plane, which is zero exactly where the operand is, so
+              // its products with a factor are infinite, or NaN with a zero, as those of
+              // the fp32 instruction.  In two planes itself and a finite value
+              // (mma_planes_inf).
+};
+
 // x[0..N) as the sum of NP bf16 planes, each the nearest bf16 value of what
-// the planes before it leave.
-template <int NP, int N, typename V> __device__ inline void split(const float *x, V (&p)[NP])
+// the planes before it leave.  (The median of NaN and two bounds is one of
+// them: a NaN is kept by the last plane.)
+template <int NP, int N, Reach R, typename V> __device__ inline void split(const float *x, V (&p)[NP])
 {
     float r[N];
 #pragma unroll
     for (int i = 0; i < N; ++i) r[i] = x[i];
 #pragma unroll
     for (int a = 0; a < NP; ++a) {
+        // bounds of plane a: the largest bf16 value, or more than a lower plane of a finite value reaches
+        constexpr float kTop = 3.38953139e38f, kRest = NP == 3 ? 0x1p121f : 256.f;
+        const bool bound = NP == 3 ? (a == 0 && R != Reach::kUnit) || (a == 1 && R == Reach::kInf) : (a == 1 && R == Reach::kInf);
+        const float lim = a == 0 ? kTop : kRest;
 #pragma unroll
         for (int i = 0; i < N; i += 2) {  // two at a time: one conversion, and the halves of its result back as floats
-            const bf16x2 h = __builtin_convertvector((f32x2{r[i], r[i + 1]}), bf16x2);
+            const float y0 = bound ? __builtin_amdgcn_fmed3f(r[i], -lim, lim) : r[i];
+            const float y1 = bound ? __builtin_amdgcn_fmed3f(r[i + 1], -lim, lim) : r[i + 1];
+            const bf16x2 h = __builtin_convertvector((f32x2{y0, y1}), bf16x2);
             p[a][i] = h[0];
             p[a][i + 1] = h[1];
             if (a + 1 < NP) {
@@ -53,6 +81,36 @@ template <int NA, int NB, typename F> __device__ inline void mma_planes(const F 
             const int j = s - i;
             if (j >= 0 && j < NB) c = mfma(a[i], b[j], c);
         }
+    }
+}
+
+// A plane with its infinities (and NaN) replaced by the largest finite value.
+template <typename F> __device__ inline F finite_plane(F x)
+{
+    typedef unsigned short words __attribute__((ext_vector_type(sizeof(F) / 2)));
+    words w;
+    __builtin_memcpy(&w, &x, sizeof(F));
+    const words top = (words)(unsigned short)0x7f7f, sign = (words)(unsigned short)0x8000;
+    w = __builtin_elementwise_min(w & ~sign, top) | (w & sign);
+    __builtin_memcpy(&x, &w, sizeof(F));
+    return x;
+}
+
+// mma_planes where a, of Reach::kInf, may hold infinities and b is a factor: in
+// one or two planes they meet b's leading plane only (its others can be zero,
+// or negative).
+template <int NA, typename F> __device__ inline void mma_planes_inf(const F (&a)[NA], const F (&b)[3], f32x4 &c)
+{
+    if constexpr (NA == 3) {
+        mma_planes(a, b, c);
+    } else {
+        const F fin = finite_plane(a[0]);
+        c = mfma(fin, b[2], c);
+        if constexpr (NA == 2) c = mfma(a[1], b[1], c);
+        c = mfma(fin, b[1], c);
+        if constexpr (NA == 2) c = mfma(a[1], b[0], c);
+        c = mfma(a[0], b[0], c);
+        if constexpr (NA == 2) __builtin_amdgcn_sched_barrier(0);  // one tile's planes at a time (fewer spills at 128 x 128)
     }
 }
 
@@ -147,7 +205,7 @@ template <typename E, int NP> __device__ inline void load_chunk(const Span &s, i
         float x[8];
 #pragma unroll
         for (int i = 0; i < 8; ++i) x[i] = static_cast<float>(e[i]);
-        split<NP, 8>(x, f);
+        split<NP, 8, Reach::kFinite>(x, f);
     }
 }
 
@@ -155,7 +213,7 @@ template <typename E, int NP> __device__ inline void load_chunk(const Span &s, i
 // from there into the NP planes of an LDS tile of row stride LD (stage), the
 // 16-byte chunks shared out over NTH threads.  Rows >= nr and columns >= nc
 // (a multiple of a chunk) are zero.
-template <typename E, int NP, int R, int D, int LD, int NTH> struct Rows {
+template <typename E, int NP, int R, int D, int LD, int NTH, Reach RC = Reach::kFinite> struct Rows {
     static constexpr int V = 16 / (int)sizeof(E), CPR = D / V, ALL = R * CPR, CH = (ALL + NTH - 1) / NTH;
     static constexpr int PLANE = R * LD;
     u32x4 c[CH];
@@ -188,7 +246,7 @@ template <typename E, int NP, int R, int D, int LD, int NTH> struct Rows {
 #pragma unroll
                 for (int i = 0; i < V; ++i) x[i] = static_cast<float>(e[i]);
                 vec p[NP];
-                split<NP, V>(x, p);
+                split<NP, V, RC>(x, p);
 #pragma unroll
                 for (int a = 0; a < NP; ++a) *reinterpret_cast<vec *>(dst + a * PLANE) = p[a];
             }
