@@ -123,6 +123,11 @@ __device__ inline float rcp1(float x)
     return __builtin_fmaf(__builtin_fmaf(-x, r, 1.f), r, r);
 }
 
+// The row statistics take the gradients times 2^-8: the sums of at most 128
+// terms e g, with e <= 1 not yet divided by their sum, then stay finite
+// wherever g is.  (Powers of two, so the bits are those without it.)
+constexpr float kStat = 0.00390625f, kUnstat = 256.f;
+
 // What the waves of a unit exchange about a row of a factor p = e^z / sum e^z
 // and its gradient g: of this wave's columns, the maximum of z, the sum of
 // e = e^(z - max), and the sum of e g.  The pull-back needs g - <p, g>, which
@@ -363,7 +368,7 @@ template <typename T, int S, int D, bool LAST, bool LENS = false> struct LBwd {
         Rows<T, NP, C, D, LDX, NTH, Reach::kInf> gr;
         qr.fetch(qb, step_l, min(max(ml, 0), C), d, tid);
         if constexpr (LAST) gr.fetch(gb, step_l, min(max(ml, 0), C), d, tid);
-        f32x4 cl[IPW], dcr[IPW];  // c_L[j][k], d c_R'[k][j]
+        f32x4 cl[IPW], dcr[IPW];  // c_L[j][k], d c_R'[k][j] times kStat
 #pragma unroll
         for (int t = 0; t < IPW; ++t) {
 #pragma unroll
@@ -371,7 +376,7 @@ template <typename T, int S, int D, bool LAST, bool LENS = false> struct LBwd {
                 const int k = (ig * IPW + t) * 16 + 4 * g + q;
                 cl[t][q] = Span(p.cL + coff + j).load1((uint32_t)(k * b) * 4, k < m);
                 dcr[t][q] = 0.f;
-                if constexpr (!LAST) dcr[t][q] = Span(p.dcR + coff + j).load1((uint32_t)(k * b) * 4, k < m);
+                if constexpr (!LAST) dcr[t][q] = kStat * Span(p.dcR + coff + j).load1((uint32_t)(k * b) * 4, k < m);
             }
             const int k = (ig * IPW + t) * 16 + c16;
             if constexpr (LAST) {
@@ -492,7 +497,7 @@ template <typename T, int S, int D, bool LAST, bool LENS = false> struct LBwd {
 #pragma unroll
                 for (int q = 0; q < 4; ++q) {
                     z[t][q] = __builtin_fmaf(z[t][q], dm.s, -cl[t][q]);
-                    w[t][q] += dcr[t][q];
+                    w[t][q] = __builtin_fmaf(w[t][q], kStat, dcr[t][q]);
                     if ((ig * IPW + t) * 16 + 4 * g + q < mk) mx = max_nan(mx, z[t][q]);
                 }
             }
@@ -511,6 +516,7 @@ template <typename T, int S, int D, bool LAST, bool LENS = false> struct LBwd {
                 __syncthreads();
             }
             st.template whole<NIG>(stat + jt * 16 + c16, C, 0.f, live);
+            const float us = dm.s * kUnstat;
             __bf16 *lrow = Ls + (jt * 16 + c16) * LDP, *wrow = Ws + (jt * 16 + c16) * LDP;
 #pragma unroll
             for (int t = 0; t < IPW; ++t) {
@@ -518,7 +524,7 @@ template <typename T, int S, int D, bool LAST, bool LENS = false> struct LBwd {
 #pragma unroll
                 for (int q = 0; q < 4; ++q) {
                     z[t][q] *= st.scale;                                  // L
-                    w[t][q] = dm.s * z[t][q] * st.centred(w[t][q]);  // dW
+                    w[t][q] = us * z[t][q] * st.centred(w[t][q]);  // dW
                 }
                 dcl[t] += w[t];
                 store_factor<Reach::kUnit>(lrow + k, H::PLP, z[t]);
@@ -794,7 +800,7 @@ template <typename T, int S, int D, bool FIRST, bool LAST, bool LENS = false> st
             // R = softmax_i and its pull-back.  The gradient of row j's logits needs d R + d c_L (log R + 1) up to
             // a constant of the row: d c_L times the logits less their maximum stands in for the second term.
             const bool live = jj < jb && (!LENS || kv > 0);  // a block of padding only has R = 0
-            const float cr = cRs[jj], dcl = dcLs[jj];
+            const float cr = cRs[jj], dcl = dcLs[jj] * kStat;
             const float sc = live ? dm.s / cr : 0.f;
             float mx = kMasked;
 #pragma unroll
@@ -815,7 +821,7 @@ template <typename T, int S, int D, bool FIRST, bool LAST, bool LENS = false> st
                     const float u = __builtin_fmaf(z[t][q], sc, -mx);
                     e4[t][q] = (ig * IPW + t) * 16 + 4 * g + q < kv ? exp_nat(u) : 0.f;
                     z[t][q] = u;
-                    w[t][q] = __builtin_fmaf(dcl, u, w[t][q]);
+                    w[t][q] = __builtin_fmaf(dcl, u, w[t][q] * kStat);
                 }
             }
             RowStat<NP == 3> st;
@@ -826,7 +832,7 @@ template <typename T, int S, int D, bool FIRST, bool LAST, bool LENS = false> st
             }
             st.template whole<NIG>(stat + jj, C, dcl, live);
             if (none) st.mx = st.scale = 0.f;
-            const float off = dcl * st.mx;
+            const float off = dcl * st.mx, us = st.scale * kUnstat;
             __bf16 *rrow = Rs + jj * LDP, *zrow = Zs + jj * LDP;
             float dzlog = 0.f;
 #pragma unroll
@@ -835,7 +841,7 @@ template <typename T, int S, int D, bool FIRST, bool LAST, bool LENS = false> st
 #pragma unroll
                 for (int q = 0; q < 4; ++q) {
                     const float r = e4[t][q] * st.scale;  // masked keys: 0
-                    const float dz = r * st.centred(w[t][q] + off);
+                    const float dz = (e4[t][q] * us) * st.centred(w[t][q] + off);
                     dzlog = __builtin_fmaf(dz, z[t][q] + st.mx, dzlog);
                     z[t][q] = r;
                     w[t][q] = dz * sc;

@@ -97,3 +97,23 @@ def test_gradient_large_v(ma, m, b, d, T):  # noqa: F811
     for name, x, r in zip(("dq", "dk", "dv"), got, ref):
         assert np.isfinite(x).all(), name
         assert oracle.rel_frobenius(x[0, 0], r) <= TOL["f32"], name
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("m,b,d,T", SHAPES)
+@pytest.mark.parametrize("down", [0, 4])
+def test_gradient_large_dout(ma, dtype, m, b, d, T, down):  # noqa: F811
+    """dO at the end of the range (times 2^-down): the sums over a row of the
+    factors' gradients, not yet divided by the sum of the weights, do not overflow."""
+    n, q, k, v, g = inputs(m, b, d, dtype)
+    plain = gpu_grads(ma, q, k, v, g, m, b, T, dtype)
+    row = n // 3
+    v *= np.float32(0.25)  # <dO, Y> within the range
+    g[0, 0, row, COL] = MAX[dtype] * np.float32(2.0 ** -down)
+    got = gpu_grads(ma, q, k, v, g, m, b, T, dtype)
+    ref = ob.autograd_grads(q[0, 0], k[0, 0], v[0, 0], g[0, 0], m, b, T)
+    rest = np.arange(d) != COL
+    assert np.array_equal(got[2][..., rest], plain[2][..., rest])
+    for name, x, r in zip(("dq", "dk", "dv"), got, ref):
+        assert np.isfinite(x).all(), name
+        assert oracle.rel_frobenius(x[0, 0], r) <= TOL[dtype], name
