@@ -338,7 +338,8 @@ int monarch_attn_release_workspace(void);
 
 /*
  * Execution path of monarch_attn_fwd (process-wide; returns the previous
- * value, or -1 on an unknown value):
+ * value, or -1 on an unknown value).  Any forced path makes the gradient's
+ * recompute run the half-steps.
  *   0  automatic (default), see below;
  *   1  one launch per half-step (the state form of the paper's
  *      Implementation paragraph, the states crossing launches through the

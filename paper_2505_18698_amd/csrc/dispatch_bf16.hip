@@ -10,8 +10,8 @@ template <> int run_exact<__bf16>(Launcher &L, const CallBufs &B, float *lse, in
 {
     return run_exact_impl<__bf16>(L, B, lse, BH, n, d);
 }
-template <> int run_bwd<__bf16>(Launcher &L, const BwdCallBufs &B, const CallDims &c)
+template <> int run_bwd<__bf16>(Launcher &L, const BwdCallBufs &B, const CallDims &c, int path)
 {
-    return run_bwd_impl<__bf16>(L, B, c);
+    return run_bwd_impl<__bf16>(L, B, c, path);
 }
 }  // namespace ma_host

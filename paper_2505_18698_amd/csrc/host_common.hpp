@@ -163,8 +163,9 @@ struct BwdCallBufs {
 // The gradient's reverse sweep for one element type and tile width (sweep_*.hip).
 template <typename T, int D> int bwd_sweep(Launcher &L, const BwdCallBufs &B, const CallDims &c);
 
-// Enqueue the gradient (forward recompute, then the reverse sweep) for one element type.
-template <typename T> int run_bwd(Launcher &L, const BwdCallBufs &B, const CallDims &c);
+// Enqueue the gradient (forward recompute, then the reverse sweep) for one
+// element type; under a forced path the recompute runs the half-steps.
+template <typename T> int run_bwd(Launcher &L, const BwdCallBufs &B, const CallDims &c, int path);
 
 // Enqueue exact softmax attention (with the row logsumexps when lse != null).
 template <typename T> int run_exact(Launcher &L, const CallBufs &B, float *lse, int64_t BH, int n, int d);

@@ -65,6 +65,40 @@ def test_bits_of_the_half_steps(ma, dtype, B, H, n, m, b, d, T):
         assert torch.equal(one, two), call.__name__
 
 
+@pytest.mark.parametrize("dtype", ["bf16", "f16"])
+@pytest.mark.parametrize("B,H,n,m,b,d,T", [
+    (3, 100, 15 * 14 - 13, 15, 14, 64, 3), (3, 100, 16 * 16, 16, 16, 72, 2), (3, 100, 9 * 7 - 2, 9, 7, 128, 2),
+    (2, 300, 4 * 16, 4, 16, 64, 2), (1, 2, 16 * 5 - 4, 16, 5, 96, 4),
+])
+def test_gradient_recompute_gives_the_bits_of_the_half_steps(ma, dtype, B, H, n, m, b, d, T):
+    """The states that the recompute keeps, of every step and for several heads
+    a workgroup: the same gradients as from the half-steps' states."""
+    import torch
+
+    td = {"bf16": torch.bfloat16, "f16": torch.float16}[dtype]
+    q, k, v = (torch.from_numpy(x).to(td).cuda() for x in si.random_qkv(B, H, n, d, dtype, seed=5, scale=1.5)[:3])
+    g = torch.from_numpy(si.random_cotangent((B, H, n, d), dtype, seed=5)).to(td).cuda()
+    lens = torch.from_numpy(si.sequence_lengths(B, n, seed=6)).cuda()
+    lens[-1] = 0
+    ma.monarch_attn_timing_enable(True)
+    try:
+        for varlen in (False, True):
+            def call():
+                out = [torch.full_like(q, float("nan")) for _ in range(3)]
+                if varlen:
+                    ma.monarch_attn_bwd_varlen(q, k, v, g, *out, lens, m, b, T)
+                else:
+                    ma.monarch_attn_bwd(q, k, v, g, *out, m, b, T)
+                return torch.stack(out), [kind for kind, _ in ma.monarch_attn_timing_read()]
+
+            (one, kinds), (two, auto) = both(ma, call)
+            assert kinds[:2 * T - 1] == ["r_half_step", "l_half_step"] * (T - 1) + ["r_half_step_final"]
+            assert auto[0] == "monarch_fused_head" and auto[1:] == kinds[2 * T - 1:]
+            assert torch.isfinite(one.float()).all() and torch.equal(one, two), varlen
+    finally:
+        ma.monarch_attn_timing_enable(False)
+
+
 def test_what_wide_small_heads_need_is_unchanged(ma):
     """d > 64: forcing the one-workgroup-per-head path stays refused, and the
     no-allocation call keeps its scratch limit."""
