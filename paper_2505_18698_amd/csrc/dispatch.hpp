@@ -289,7 +289,8 @@ template <typename T> int run_call_impl(Launcher &L, const CallBufs &B, const Ca
                                          : "the grouped kernel needs bf16/fp16, d <= 64, m <= 64, b <= 32, no lengths, "
                                            "no pre-padding and no objective");
     int rc;
-    if (fam == kFamFused || (path == kAuto && small_heads(dtype, c.m, c.b))) {
+    if (fam == kFamFused ||
+        (path == kAuto && small_heads(dtype, c.m, c.b) && one_launch_forward(c.BH, c.d, c.m, c.b, c.T, B.lens != nullptr))) {
         if constexpr (sizeof(T) == 2)
             rc = run_fused<T>(L, B, hd, c);
         else
@@ -329,9 +330,8 @@ template <typename T, int D> int run_bwd_d(Launcher &L, const BwdCallBufs &B, co
     int rc;
     if constexpr (sizeof(T) == 2) {
         // small heads: one launch of the one-workgroup-per-head kernel, the
-        // states to memory as it goes (384 heads of 15 x 14 rows, T = 2: 19.6 us
-        // against 27.5 us for three half-step launches)
-        if (path == kAuto && small_heads(MA_BF16, c.m, c.b)) {
+        // states to memory as it goes
+        if (path == kAuto && small_heads(MA_BF16, c.m, c.b) && one_launch_recompute(c.BH, c.d, c.T)) {
             const CallBufs f{B.q, B.k, B.v, nullptr, B.aR, B.aL, B.Y, B.cR, B.cL, nullptr, nullptr, B.lens};
             if ((rc = run_fused_states<T>(L, f, hd, c, (int64_t)(B.st / sizeof(T)), (int64_t)B.cst)) != MA_OK) return rc;
             return bwd_sweep<T, D>(L, B, c);

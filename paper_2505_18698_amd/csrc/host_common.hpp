@@ -113,13 +113,37 @@ inline bool grouped_applies(int32_t dtype, int64_t d, int64_t m, int64_t b, bool
     return (dtype == MA_BF16 || dtype == MA_F16) && d <= 64 && m <= 64 && b <= 32 && !lens && !obj;
 }
 
-// Heads of up to 16 blocks of up to 16 rows.  Where the automatic path gives
-// them to the half-steps (d > 64, beyond fused_applies), the half-steps'
-// launches are one of the one-workgroup-per-head kernel, which takes any d;
-// the workspace rules stay those of the half-steps.
+// Heads of up to 16 blocks of up to 16 rows.
 inline bool small_heads(int32_t dtype, int64_t m, int64_t b)
 {
     return (dtype == MA_BF16 || dtype == MA_F16) && m <= 16 && b <= 16;
+}
+
+// Small heads that the automatic path gives to the half-steps (d > 64, beyond
+// fused_applies): whether the half-steps' launches are one of the
+// one-workgroup-per-head kernel, which takes any d (the workspace rules stay
+// those of the half-steps).  Not for one step of few large heads, which two
+// launches spread over m and b workgroups a head.  Times against the
+// half-steps': one step at 128 columns, 4 heads: 16 x 16 rows 1.19 (8.5 us),
+// 15 x 14 1.11, 16 x 4 0.99, 8 x 8 0.94, with lengths 1.22, 1.16, 1.03, 1.00;
+// 24 heads of 16 x 16 1.01, 32 heads 0.95.  At 96 columns 16 x 16 rows 1.06 for
+// 4 heads, 1.01 for 12, 0.94 for 24; smaller heads 0.85 to 0.99.  Two steps:
+// 0.57 to 0.85 for any head.
+inline bool one_launch_forward(int64_t BH, int64_t d, int64_t m, int64_t b, int T, bool lens)
+{
+    const bool wide = tile_d(d) == 128;
+    const int64_t rows = wide ? (lens ? 64 : 144) : 256;
+    return T > 1 || m * b < rows || BH >= (wide ? 24 : 12);
+}
+
+// The same for the gradient's recompute, at any d.  One step is one launch on
+// the half-steps too, of m workgroups a head: the whole gradient takes 1.0 to
+// 1.4 times as long with one (4 to 256 heads; 1.0 to 1.17 from 384 to 2048).
+// Two steps are three launches: 0.90 to 1.0 of them, but 1.0 to 1.16 at 128
+// columns below 64 heads; three steps 0.85 to 1.06 of five.
+inline bool one_launch_recompute(int64_t BH, int64_t d, int T)
+{
+    return T > 2 || (T == 2 && (tile_d(d) < 128 || BH >= 64));
 }
 
 // The family that runs a call under `path` (kFamNone: the forced path does

@@ -99,6 +99,38 @@ def test_gradient_recompute_gives_the_bits_of_the_half_steps(ma, dtype, B, H, n,
         ma.monarch_attn_timing_enable(False)
 
 
+@pytest.mark.parametrize("B,H,m,b,d,T,forward,recompute", [
+    (1, 23, 16, 16, 128, 1, False, False), (1, 24, 16, 16, 128, 1, True, False), (1, 4, 15, 14, 104, 1, False, False),
+    (1, 11, 16, 16, 96, 1, False, False), (1, 12, 16, 16, 72, 1, True, False), (1, 4, 15, 14, 96, 1, True, False),
+    (1, 4, 8, 8, 128, 1, True, False), (3, 300, 16, 16, 64, 1, True, False), (1, 2, 16, 16, 64, 2, True, True),
+    (1, 63, 16, 16, 128, 2, True, False), (2, 32, 16, 16, 128, 2, True, True), (1, 2, 4, 16, 96, 2, True, True),
+    (1, 1, 16, 16, 128, 3, True, True),
+])
+def test_one_launch_where_it_is_faster(ma, B, H, m, b, d, T, forward, recompute):
+    """The lines of the automatic path: one step of few large heads, and the
+    recompute of one step, run on the half-steps."""
+    import torch
+
+    q, k, v, g = (torch.randn(B, H, m * b, d, device="cuda", dtype=torch.bfloat16) for _ in range(4))
+    out, grads = torch.empty_like(q), [torch.empty_like(q) for _ in range(3)]
+    ma.monarch_attn_timing_enable(True)
+    try:
+        ma.monarch_attn_fwd(q, k, v, out, m, b, T)
+        assert [kind for kind, _ in ma.monarch_attn_timing_read()] == (
+            ["monarch_fused_head"] if forward else ["r_half_step_final", "monarch_apply"])
+        lens = torch.full((B,), m * b, device="cuda", dtype=torch.int32)
+        ma.monarch_attn_fwd_varlen(q, k, v, out, lens, m, b, T)
+        few = T == 1 and d > 96 and m * b >= 64 and B * H < 24  # with lengths, heads of 64 rows up
+        assert [kind for kind, _ in ma.monarch_attn_timing_read()] == (
+            ["monarch_fused_head"] if forward and not few else ["r_half_step_final", "monarch_apply"])
+        ma.monarch_attn_bwd(q, k, v, g, *grads, m, b, T)
+        kinds = [kind for kind, _ in ma.monarch_attn_timing_read()]
+        half = ["r_half_step", "l_half_step"] * (T - 1) + ["r_half_step_final"]
+        assert kinds == (["monarch_fused_head"] if recompute else half) + ["l_bwd", "r_bwd"] * T
+    finally:
+        ma.monarch_attn_timing_enable(False)
+
+
 def test_what_wide_small_heads_need_is_unchanged(ma):
     """d > 64: forcing the one-workgroup-per-head path stays refused, and the
     no-allocation call keeps its scratch limit."""
