@@ -7,49 +7,39 @@
 
 namespace ma_host {
 
-template <typename T, int D, bool RGB, bool RGM, bool LENS, bool TWO>
-int launch_fused1(Launcher &L, const CallBufs &B, ma::HeadDims hd, const CallDims &c)
+// One workgroup a head, or as many as are resident at once, each looping over heads.
+template <typename U> dim3 head_grid(const void *kern, const CallDims &c)
+{
+    if (!U::LOOP) return dim3((unsigned)c.BH);
+    const int64_t cap = (int64_t)resident_per_cu(kern, U::NTH) * c.num_cus;
+    return dim3((unsigned)(c.BH < cap ? c.BH : cap));
+}
+
+template <typename T, int D, bool RGB, bool RGM, bool LENS = false>
+int launch_fused(Launcher &L, const CallBufs &B, const ma::HeadDims &hd, const CallDims &c)
 {
     using U = ma::FusedHead<T, D, RGB, RGM, LENS>;
-    auto kern = ma::monarch_fused_head<T, D, RGB, RGM, LENS, TWO>;
-    // as many workgroups as are resident at once, each looping over heads
-    const int64_t cap = (int64_t)resident_per_cu((const void *)kern, U::NTH) * c.num_cus;
-    const int64_t grid = c.BH < cap ? c.BH : cap;
-    hd.units = c.BH;
+    auto kern = ma::monarch_fused_head<T, D, RGB, RGM, LENS>;
+    const dim3 grid = head_grid<U>((const void *)kern, c);
     const ma::Bufs<T> p = typed<T>(B);
     const int64_t BH = c.BH;
     const int T_ = c.T;
     return L.run(kFused, [&] {
-        return launched([&] { hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(U::NTH), 0, L.stream, p, hd, BH, T_); });
+        return launched([&] { hipLaunchKernelGGL(kern, grid, dim3(U::NTH), 0, L.stream, p, hd, BH, T_); });
     });
 }
 
-// Two heads a compute unit where there are more heads than units and their LDS
-// allows it (D = 64); else the registers of one, without spills (256 heads of 8
-// x 8 rows with lengths: 5.6 us against 6.5; 512 of 5 x 11 without: 11.1 us, 13.4
-// with one head a unit in the kernel before).
 template <typename T, int D, bool RGB, bool RGM, bool LENS = false>
-int launch_fused(Launcher &L, const CallBufs &B, ma::HeadDims hd, const CallDims &c)
-{
-    if constexpr (D == 64) {
-        if (c.BH > c.num_cus) return launch_fused1<T, D, RGB, RGM, LENS, true>(L, B, hd, c);
-    }
-    return launch_fused1<T, D, RGB, RGM, LENS, false>(L, B, hd, c);
-}
-
-template <typename T, int D, bool RGB, bool RGM, bool LENS = false>
-int launch_states(Launcher &L, const CallBufs &B, ma::HeadDims hd, const CallDims &c, const ma::KeptStates<T> &keep)
+int launch_states(Launcher &L, const CallBufs &B, const ma::HeadDims &hd, const CallDims &c, const ma::KeptStates<T> &keep)
 {
     using U = ma::FusedHead<T, D, RGB, RGM, LENS, true>;
     auto kern = ma::monarch_fused_states<T, D, RGB, RGM, LENS>;
-    const int64_t cap = (int64_t)resident_per_cu((const void *)kern, U::NTH) * c.num_cus;
-    const int64_t grid = c.BH < cap ? c.BH : cap;
+    const dim3 grid = head_grid<U>((const void *)kern, c);
     const ma::Bufs<T> p = typed<T>(B);
     const int64_t BH = c.BH;
     const int T_ = c.T;
     return L.run(kFused, [&] {
-        return launched(
-            [&] { hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(U::NTH), 0, L.stream, p, hd, BH, T_, keep); });
+        return launched([&] { hipLaunchKernelGGL(kern, grid, dim3(U::NTH), 0, L.stream, p, hd, BH, T_, keep); });
     });
 }
 

@@ -49,6 +49,13 @@ template <typename T, int D, bool RGB, bool RGM, bool LENS = false, bool KEEP = 
     static_assert(!LENS || (RGB && RGM), "per-sequence lengths need the masked softmaxes");
     static_assert(sizeof(T) == 2, "16-bit elements only");
     using M = Mma<T>;
+    // Where LDS holds two heads a compute unit (D = 64), a workgroup takes one
+    // head: without the loop's values a wave needs 60 VGPRs, and two heads fit the
+    // registers without spills (2048 heads of 16 x 16 rows, one step: 53 -> 47 us
+    // with lengths; of 15 x 14, 40 -> 37).  Wider tiles hold one head, and a
+    // workgroup that loops starts the next sooner than a new one does (2048 heads
+    // of 15 x 14 rows, d = 72, T = 1: 52 us against 60).
+    static constexpr bool LOOP = D > 64;
     static constexpr int NTH = 1024, LD = D + 8, NC = D / M::KC, NV = D / 16;
     // Blocks of 16 slots are BS elements apart: 16 rows plus 16 bytes, so that
     // the 16 lanes reading row r of 16 different blocks hit different LDS banks.
@@ -252,7 +259,7 @@ template <typename T, int D, bool RGB, bool RGM, bool LENS = false, bool KEEP = 
                         c.lane, c.d);
     }
 
-    // Heads blockIdx.x, blockIdx.x + gridDim.x, ... < BH.
+    // Head blockIdx.x (LOOP: and blockIdx.x + gridDim.x, ... < BH).
     __device__ static void run(const Bufs<T> &p, const HeadDims &hd, int64_t BH, int T_, const KeptStates<T> &keep,
                                char *lds)
     {
@@ -274,7 +281,7 @@ template <typename T, int D, bool RGB, bool RGM, bool LENS = false, bool KEEP = 
         c.g = c.lane >> 4;
         c.c16 = c.lane & 15;
 
-        for (int64_t bh = blockIdx.x; bh < BH; bh += gridDim.x) {
+        for (int64_t bh = blockIdx.x;;) {
             c.bh = bh;
             const int64_t hoff = bh * (int64_t)c.n * c.d;
             const Span qs(p.q + hoff), ks(p.k + hoff), vs(p.v + hoff);
@@ -316,15 +323,16 @@ template <typename T, int D, bool RGB, bool RGM, bool LENS = false, bool KEEP = 
                 __syncthreads();
             }
             if (!KEEP && w < c.b) apply_unit(c, w, un, p.out + hoff);
-            if (bh + gridDim.x < BH) __syncthreads();  // the next head overwrites A and K
+            if constexpr (!LOOP) return;
+            bh += gridDim.x;
+            if (bh >= BH) return;
+            __syncthreads();  // the next head overwrites A and K
         }
     }
 };
 
-// TWO: registers for two heads a compute unit (64 VGPRs, a few spilled in the
-// masked forms), for calls with more heads than compute units.
-template <typename T, int D, bool RGB, bool RGM, bool LENS, bool TWO>
-__global__ __launch_bounds__(1024, TWO ? 8 : 4) void monarch_fused_head(Bufs<T> p, HeadDims hd, int64_t BH, int T_)
+template <typename T, int D, bool RGB, bool RGM, bool LENS>
+__global__ __launch_bounds__(1024, D == 64 ? 8 : 4) void monarch_fused_head(Bufs<T> p, HeadDims hd, int64_t BH, int T_)
 {
     using U = FusedHead<T, D, RGB, RGM, LENS>;
     __shared__ __attribute__((aligned(16))) char lds[U::LDS_BYTES];
@@ -332,10 +340,9 @@ __global__ __launch_bounds__(1024, TWO ? 8 : 4) void monarch_fused_head(Bufs<T> 
 }
 
 // The gradient's recompute of small heads: every step's states to memory, as
-// whole rows from the registers that hold them.  That takes 84 VGPRs at
-// D = 64, so one head a compute unit; holding it to 64 for two spills (384
-// heads of 15 x 14 rows, T = 2: 28 us against 19.6, and against 27.5 us on the
-// half-steps).
+// whole rows from the registers that hold them.  At D = 64 that takes 66 VGPRs,
+// so one head a compute unit; held to 64, with spills, 4 heads of 15 x 14 rows
+// take 4% longer a gradient (T = 2) and 2048 heads as long.
 template <typename T, int D, bool RGB, bool RGM, bool LENS>
 __global__ __launch_bounds__(1024, 4) void monarch_fused_states(Bufs<T> p, HeadDims hd, int64_t BH, int T_, KeptStates<T> keep)
 {
