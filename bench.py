@@ -637,8 +637,9 @@ def quality(ma, torch, w, steps_list=(1, 2, 3)):
 # definitions and their launch configuration (the gradient's launches live
 # apart, so that changing them leaves the forward records valid).
 CSRC = os.path.join(ROOT, "paper_2505_18698_amd", "csrc")
-FWD_SOURCES = ("tiles.hpp", "planes.hpp", "half_f32.hpp", "ma_kernels.hpp", "fused.hpp", "grouped.hpp", "dispatch.hpp")
-BWD_SOURCES = ("backward.hpp", "dispatch_bwd.hpp", "tiles.hpp", "planes.hpp", "half_f32.hpp", "ma_kernels.hpp", "fused.hpp", "grouped.hpp", "dispatch.hpp")
+FWD_SOURCES = ("tiles.hpp", "planes.hpp", "half_f32.hpp", "ma_kernels.hpp", "fused.hpp", "grouped.hpp", "dispatch.hpp",
+               "dispatch_fused.hpp", "launch.hpp", "host_common.hpp")
+BWD_SOURCES = ("backward.hpp", "dispatch_bwd.hpp") + FWD_SOURCES
 
 
 def kernel_sources_sha(kernel):
