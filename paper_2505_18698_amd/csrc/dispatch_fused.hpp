@@ -10,7 +10,7 @@ namespace ma_host {
 // One workgroup a head, or as many as are resident at once, each looping over heads.
 template <typename U> dim3 head_grid(const void *kern, const CallDims &c)
 {
-    if (!U::LOOP) return dim3((unsigned)c.BH);
+    if (!U::LOOP) return c.BH <= U::ROW ? dim3((unsigned)c.BH) : dim3(U::ROW, (unsigned)((c.BH + U::ROW - 1) / U::ROW));
     const int64_t cap = (int64_t)resident_per_cu(kern, U::NTH) * c.num_cus;
     return dim3((unsigned)(c.BH < cap ? c.BH : cap));
 }

@@ -56,6 +56,9 @@ template <typename T, int D, bool RGB, bool RGM, bool LENS = false, bool KEEP = 
     // workgroup that loops starts the next sooner than a new one does (2048 heads
     // of 15 x 14 rows, d = 72, T = 1: 52 us against 60).
     static constexpr bool LOOP = D > 64;
+    // One head a workgroup: ROW workgroups a row of the grid, as a grid dimension
+    // of 1024-thread workgroups ends below 2^22 of them.
+    static constexpr int LOG_ROW = 21, ROW = 1 << LOG_ROW;
     static constexpr int NTH = 1024, LD = D + 8, NC = D / M::KC, NV = D / 16;
     // Blocks of 16 slots are BS elements apart: 16 rows plus 16 bytes, so that
     // the 16 lanes reading row r of 16 different blocks hit different LDS banks.
@@ -259,7 +262,7 @@ template <typename T, int D, bool RGB, bool RGM, bool LENS = false, bool KEEP = 
                         c.lane, c.d);
     }
 
-    // Head blockIdx.x (LOOP: and blockIdx.x + gridDim.x, ... < BH).
+    // Head blockIdx.x of row blockIdx.y (LOOP: heads blockIdx.x, blockIdx.x + gridDim.x, ... < BH).
     __device__ static void run(const Bufs<T> &p, const HeadDims &hd, int64_t BH, int T_, const KeptStates<T> &keep,
                                char *lds)
     {
@@ -281,7 +284,12 @@ template <typename T, int D, bool RGB, bool RGM, bool LENS = false, bool KEEP = 
         c.g = c.lane >> 4;
         c.c16 = c.lane & 15;
 
-        for (int64_t bh = blockIdx.x;;) {
+        int64_t bh = blockIdx.x;
+        if constexpr (!LOOP) {
+            bh += (int64_t)blockIdx.y << LOG_ROW;
+            if (bh >= BH) return;
+        }
+        for (;;) {
             c.bh = bh;
             const int64_t hoff = bh * (int64_t)c.n * c.d;
             const Span qs(p.q + hoff), ks(p.k + hoff), vs(p.v + hoff);

@@ -79,3 +79,32 @@ def test_gradient_beyond_2_to_the_31_elements(ma):
     del q, k, v, g, grads
     torch.cuda.empty_cache()
     ma.monarch_attn_release_workspace()
+
+
+def test_more_small_heads_than_one_grid_row(ma):
+    """2^22 + 5 heads (at 1024 threads a head more than one grid dimension takes): one
+    query and one key a head make O = V and dV = dO, and heads around the ends of
+    the grid's rows have the gradients of a call of their own."""
+    import torch
+
+    H, d = (1 << 22) + 5, 8
+    _need(torch, 16)
+    q, k, v, g = (torch.randn(1, H, 1, d, device="cuda").to(torch.bfloat16) for _ in range(4))
+    lens = torch.ones(1, dtype=torch.int32, device="cuda")
+    for call in (lambda o: ma.monarch_attn_fwd(q, k, v, o, 1, 1, 2),
+                 lambda o: ma.monarch_attn_fwd_varlen(q, k, v, o, lens, 1, 1, 2)):
+        out = torch.full_like(v, float("nan"))
+        call(out)
+        assert torch.equal(out, v)
+    dq, dk, dv = (torch.full_like(q, float("nan")) for _ in range(3))
+    ma.monarch_attn_bwd(q, k, v, g, dq, dk, dv, 1, 1, 2)
+    torch.cuda.synchronize()
+    assert torch.equal(dv, g)
+    for h in (0, (1 << 21) - 500, (1 << 22) - 500):
+        part = [x[:, h:h + 505].contiguous() for x in (q, k, v, g)]
+        grads = [torch.full_like(part[0], float("nan")) for _ in range(3)]
+        ma.monarch_attn_bwd(*part, *grads, 1, 1, 2)
+        assert torch.equal(torch.stack(grads), torch.stack([x[:, h:h + 505] for x in (dq, dk, dv)]))
+    del q, k, v, g, out, dq, dk, dv, part, grads
+    torch.cuda.empty_cache()
+    ma.monarch_attn_release_workspace()
