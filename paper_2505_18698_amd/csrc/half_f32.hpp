@@ -196,13 +196,43 @@ template <int NB, int D, bool FIRST, bool FINAL, bool RAGGED, bool LENS = false>
 template <int NM, int D, bool RAGGED, bool LENS> struct LBase32 {
     static constexpr int NT = NM / 16, W = NT, NTH = 64 * W, LD = D + 16, PLANE = NM * LD;
     using Tile = Rows<float, 3, NM, D, LD, NTH>;
+    // alpha_L[j], which only the scores read: with one wave straight into its
+    // registers.  Through LDS (15.4 KB a workgroup instead of 9.3 and 7.7) ten
+    // waves shared a compute unit, fewer than the registers allow: 1865 heads of
+    // 2 x 63 rows, d = 16: apply 204 -> 125 us; 232 heads of 2 x 123, d = 64: L
+    // 49.2 -> 30.1, apply 51.6 -> 32.7; 1024 heads of 16 x 32: L 90 -> 84, apply
+    // 131 -> 119; 64 such heads 8.5 and 10.1 either way.
+    static constexpr bool DIRECT = NT == 1;
+    using ATile = typename std::conditional<DIRECT, RowRaw<D>, Tile>::type;
+    static constexpr int A_BYTES = DIRECT ? 0 : 3 * PLANE * 2;
+
+    __device__ static void fetch_a(const Bufs<float> &p, int64_t hoff, int j, int m, int d, int tid, ATile &at)
+    {
+        const float *base = p.aL + hoff + (int64_t)j * m * d;
+        const int r = tid & 15;
+        if constexpr (DIRECT)
+            at.load(Span(base), r * d, r < m, tid >> 4, d);
+        else
+            at.fetch(base, d, m, d, tid);
+    }
     using YTile = Rows<float, 3, NM, D, LD, NTH, Reach::kInf>;
 
     // Z (log2 units) of the wave's rows: lane holds k = 16t + 4g + qq of row l = 16 wave + c16.
-    __device__ static void logits(const HeadDims &hd, const __bf16 *As, const float *cLs, const bf16x8 (&bf)[D / 32][3],
-                                  f32x4 (&sc)[NT], int g, int c16)
+    __device__ static void logits(const HeadDims &hd, const ATile &at, const __bf16 *As, const float *cLs,
+                                  const bf16x8 (&bf)[D / 32][3], f32x4 (&sc)[NT], int g, int c16)
     {
-        scores32<NT, D>(As, PLANE, LD, bf, sc, g, c16);
+        if constexpr (DIRECT) {
+            Score<true> acc;
+#pragma unroll
+            for (int c = 0; c < D / 32; ++c) {
+                bf16x8 a[3];
+                at.planes(c, false, a);
+                acc.add(a, bf[c]);
+            }
+            sc[0] = acc.value();
+        } else {
+            scores32<NT, D>(As, PLANE, LD, bf, sc, g, c16);
+        }
 #pragma unroll
         for (int t = 0; t < NT; ++t) {
             const f32x4 bias = *reinterpret_cast<const f32x4 *>(cLs + 16 * t + 4 * g);
@@ -247,11 +277,12 @@ template <int NM, int D, bool RAGGED, bool LENS = false> struct LHalf32 : LBase3
     using typename B::Tile;
     static constexpr int NT = B::NT, W = B::W, NTH = B::NTH, LD = B::LD, PLANE = B::PLANE, LDP = NM + 8;
     // Qbar[j]; alpha_L[j], then P in fp32
-    static constexpr int Q_BYTES = 3 * PLANE * 2, AP_BYTES = Q_BYTES > NM * LDP * 4 ? Q_BYTES : NM * LDP * 4;
+    static constexpr int Q_BYTES = 3 * PLANE * 2, P_BYTES = NM * LDP * 4, AP_BYTES = B::A_BYTES > P_BYTES ? B::A_BYTES : P_BYTES;
     static constexpr int LDS_BYTES = Q_BYTES + AP_BYTES + NM * 4 + W * 4;
 
     struct Regs {
-        Tile qt, at;
+        Tile qt;
+        typename B::ATile at;
         float cl;
         int nl, j;
     };
@@ -267,7 +298,7 @@ template <int NM, int D, bool RAGGED, bool LENS = false> struct LHalf32 : LBase3
         }
         const int ml = (hd.n - j + b - 1) / b;  // rows l of class j in memory: l*b + j < n
         gr.qt.fetch(p.q + bh * (int64_t)hd.n * d, (int)rstep<RV>(hd, b) * d, ml, d, tid, (int)mrow_u<RV>(hd, j) * d);
-        gr.at.fetch(p.aL + bh * N * d + (int64_t)j * m * d, d, m, d, tid);
+        B::fetch_a(p, bh * N * d, j, m, d, tid, gr.at);
         gr.cl = tid < m ? p.cL[bh * N + (int64_t)tid * b + j] : 0.f;
     }
 
@@ -280,7 +311,7 @@ template <int NM, int D, bool RAGGED, bool LENS = false> struct LHalf32 : LBase3
                 if ((tid + h * NTH) / Tile::CPR >= ml) gr.qt.c[h] = u32x4{0u, 0u, 0u, 0u};
         }
         gr.qt.stage(reinterpret_cast<__bf16 *>(lds), tid);
-        gr.at.stage(reinterpret_cast<__bf16 *>(lds + Q_BYTES), tid);
+        if constexpr (!B::DIRECT) gr.at.stage(reinterpret_cast<__bf16 *>(lds + Q_BYTES), tid);
         if (tid < NM) reinterpret_cast<float *>(lds + Q_BYTES + AP_BYTES)[tid] = gr.cl * kLog2e;
     }
 
@@ -300,7 +331,7 @@ template <int NM, int D, bool RAGGED, bool LENS = false> struct LHalf32 : LBase3
             bf16x8 bf[D / 32][3];
 #pragma unroll
             for (int c = 0; c < D / 32; ++c) read_chunk<3>(Qs + l * LD, PLANE, c, g, bf[c]);
-            B::logits(hd, As, cLs, bf, sc, g, c16);
+            B::logits(hd, gr.at, As, cLs, bf, sc, g, c16);
         }
         const bool logp = hd.colnorm;  // P holds log2 L (below)
         f32x4 zk[NT];
@@ -371,10 +402,10 @@ template <int NM, int D, bool RAGGED, bool LENS = false> struct Apply32 : LBase3
     using B = LBase32<NM, D, RAGGED, LENS>;
     using typename B::Tile;
     static constexpr int NT = B::NT, W = B::W, NTH = B::NTH, LD = B::LD, PLANE = B::PLANE;
-    static constexpr int T_BYTES = 3 * PLANE * 2, LDS_BYTES = 2 * T_BYTES + NM * 4 + W * 4;  // alpha_L[j], Y[j]
+    static constexpr int Y_BYTES = 3 * PLANE * 2, LDS_BYTES = B::A_BYTES + Y_BYTES + NM * 4 + W * 4;  // alpha_L[j], Y[j]
 
     struct Regs {
-        Tile at;
+        typename B::ATile at;
         typename B::YTile yt;
         float cl;
         RowRaw<D> row;  // row l of Qbar[j]
@@ -386,7 +417,7 @@ template <int NM, int D, bool RAGGED, bool LENS = false> struct Apply32 : LBase3
     {
         const int m = hd.m, b = hd.b, d = head_dim<DK>(hd.d);
         const int64_t N = (int64_t)m * b, hoff = bh * N * d;
-        gr.at.fetch(p.aL + hoff + (int64_t)j * m * d, d, m, d, tid);
+        B::fetch_a(p, hoff, j, m, d, tid, gr.at);
         gr.yt.fetch(p.Y + hoff + (int64_t)j * m * d, d, m, d, tid);
         const int l = (tid >> 6) * 16 + (tid & 15);
         gr.row.load(Span(p.q + bh * (int64_t)hd.n * d), ((int)mrow_u<RV>(hd, j) + l * (int)rstep<RV>(hd, b)) * d, l * b + j < hd.n,
@@ -397,17 +428,17 @@ template <int NM, int D, bool RAGGED, bool LENS = false> struct Apply32 : LBase3
 
     __device__ static void stage(const HeadDims &, Regs &gr, char *lds, int tid)
     {
-        gr.at.stage(reinterpret_cast<__bf16 *>(lds), tid);
-        gr.yt.stage(reinterpret_cast<__bf16 *>(lds + T_BYTES), tid);
-        if (tid < NM) reinterpret_cast<float *>(lds + 2 * T_BYTES)[tid] = gr.cl * kLog2e;
+        if constexpr (!B::DIRECT) gr.at.stage(reinterpret_cast<__bf16 *>(lds), tid);
+        gr.yt.stage(reinterpret_cast<__bf16 *>(lds + B::A_BYTES), tid);
+        if (tid < NM) reinterpret_cast<float *>(lds + B::A_BYTES + Y_BYTES)[tid] = gr.cl * kLog2e;
     }
 
     // After stage() and a barrier.
     template <int DK, bool RV>
     __device__ static void compute(const Bufs<float> &p, const HeadDims &hd, int64_t bh, int j, Regs &gr, char *lds, int tid)
     {
-        const __bf16 *As = reinterpret_cast<const __bf16 *>(lds), *Ys = reinterpret_cast<const __bf16 *>(lds + T_BYTES);
-        float *cLs = reinterpret_cast<float *>(lds + 2 * T_BYTES);
+        const __bf16 *As = reinterpret_cast<const __bf16 *>(lds), *Ys = reinterpret_cast<const __bf16 *>(lds + B::A_BYTES);
+        float *cLs = reinterpret_cast<float *>(lds + B::A_BYTES + Y_BYTES);
         const int m = hd.m, b = hd.b, d = head_dim<DK>(hd.d), nl = LENS ? gr.nl : hd.n;
         const int lane = tid & 63, g = lane >> 4, c16 = lane & 15, l = (tid >> 6) * 16 + c16;
         const int mk = LENS ? live_blocks(m, b, nl) : m;  // blocks k >= mk: no real key
@@ -416,7 +447,7 @@ template <int NM, int D, bool RAGGED, bool LENS = false> struct Apply32 : LBase3
 #pragma unroll
         for (int c = 0; c < D / 32; ++c) gr.row.planes(c, LENS && row >= nl, bf[c]);
         f32x4 sc[NT];
-        B::logits(hd, As, cLs, bf, sc, g, c16);
+        B::logits(hd, gr.at, As, cLs, bf, sc, g, c16);
         float mx;
         const float sum = B::softmax(sc, mk, g, mx);
         const bool any = !LENS || mk > 0;  // a head without a real key has L = 0

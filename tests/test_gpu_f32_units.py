@@ -27,6 +27,7 @@ def ma():
 @pytest.mark.parametrize("n,m,b,d,T", [
     (16 * 16, 16, 16, 64, 2), (17 * 33 - 5, 17, 33, 96, 2), (64 * 64, 64, 64, 128, 2), (65 * 16, 65, 16, 64, 3),
     (128 * 128 - 7, 128, 128, 64, 2), (1, 1, 1, 4, 2), (31 * 5, 31, 5, 100, 1), (5 * 127, 5, 127, 60, 2),
+    (9 * 20 - 3, 9, 20, 88, 2), (16 * 12, 16, 12, 128, 3),
 ])
 def test_units(ma, n, m, b, d, T):
     import torch
@@ -49,3 +50,18 @@ def test_units(ma, n, m, b, d, T):
     var = var.double().cpu().numpy()
     ref = oracle.monarch_attention_varlen(q, k, v, lens, m, b, T)
     assert np.isfinite(var).all() and oracle.rel_frobenius(var, ref) <= TOL
+
+
+@pytest.mark.parametrize("m,b,d", [(9, 20, 64), (16, 12, 96), (2, 63, 128)])
+def test_workgroups_that_take_several_units(ma, m, b, d):
+    """More units than the device holds at once (12 waves a compute unit at
+    most): every head's bits are those of a call on that head alone."""
+    import torch
+
+    H, n = 400, m * b - 1
+    q, k, v = (torch.randn(1, H, n, d, device="cuda") for _ in range(3))
+    out = ma.monarch_attn_fwd(q, k, v, torch.full_like(q, float("nan")), m, b, 2)
+    for h in (0, 201, H - 1):
+        one = [x[:, h:h + 1].contiguous() for x in (q, k, v)]
+        alone = ma.monarch_attn_fwd(*one, torch.full_like(one[0], float("nan")), m, b, 2)
+        assert torch.equal(alone[0, 0], out[0, h])
