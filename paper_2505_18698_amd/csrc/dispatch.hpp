@@ -290,7 +290,7 @@ template <typename T> int run_call_impl(Launcher &L, const CallBufs &B, const Ca
                                            "no pre-padding and no objective");
     int rc;
     if (fam == kFamFused ||
-        (path == kAuto && small_heads(dtype, c.m, c.b) && one_launch_forward(c.BH, c.d, c.m, c.b, c.T, B.lens != nullptr))) {
+        (path == kAuto && small_heads(dtype, c.m, c.b) && one_launch_forward(c.BH, c.d, c.m, c.b, c.T, B.lens != nullptr, c.num_cus))) {
         if constexpr (sizeof(T) == 2)
             rc = run_fused<T>(L, B, hd, c);
         else
@@ -331,7 +331,7 @@ template <typename T, int D> int run_bwd_d(Launcher &L, const BwdCallBufs &B, co
     if constexpr (sizeof(T) == 2) {
         // small heads: one launch of the one-workgroup-per-head kernel, the
         // states to memory as it goes
-        if (path == kAuto && small_heads(MA_BF16, c.m, c.b) && one_launch_recompute(c.BH, c.d, c.T)) {
+        if (path == kAuto && small_heads(MA_BF16, c.m, c.b) && one_launch_recompute(c.BH, c.d, c.m, c.b, c.T, c.num_cus)) {
             const CallBufs f{B.q, B.k, B.v, nullptr, B.aR, B.aL, B.Y, B.cR, B.cL, nullptr, nullptr, B.lens};
             if ((rc = run_fused_states<T>(L, f, hd, c, (int64_t)(B.st / sizeof(T)), (int64_t)B.cst)) != MA_OK) return rc;
             return bwd_sweep<T, D>(L, B, c);

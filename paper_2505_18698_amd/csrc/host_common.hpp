@@ -119,31 +119,59 @@ inline bool small_heads(int32_t dtype, int64_t m, int64_t b)
     return (dtype == MA_BF16 || dtype == MA_F16) && m <= 16 && b <= 16;
 }
 
+// Whether heads that take a compute unit each, in rounds of num_cus, are large
+// enough for their rounds: one of few units (m + b, which the half-steps run a
+// dozen a compute unit) leaves it idle.  Any up to `free` rounds; from 16 units
+// up always; between them `base` units and `quarters` / 4 a round, begun rounds
+// counting whole.
+inline bool fills_rounds(int64_t BH, int64_t units, int64_t num_cus, int64_t free, int64_t base, int64_t quarters)
+{
+    const int64_t rounds = (BH + num_cus - 1) / num_cus;
+    return rounds <= free || units >= 16 || 4 * (units - base) >= quarters * rounds;
+}
+
 // Small heads that the automatic path gives to the half-steps (d > 64, beyond
 // fused_applies): whether the half-steps' launches are one of the
 // one-workgroup-per-head kernel, which takes any d (the workspace rules stay
-// those of the half-steps).  Not for one step of few large heads, which two
-// launches spread over m and b workgroups a head.  Times against the
-// half-steps': one step at 128 columns, 4 heads: 16 x 16 rows 1.19 (8.5 us),
-// 15 x 14 1.11, 16 x 4 0.99, 8 x 8 0.94, with lengths 1.22, 1.16, 1.03, 1.00;
-// 24 heads of 16 x 16 1.01, 32 heads 0.95.  At 96 columns 16 x 16 rows 1.06 for
-// 4 heads, 1.01 for 12, 0.94 for 24; smaller heads 0.85 to 0.99.  Two steps:
-// 0.57 to 0.85 for any head.
-inline bool one_launch_forward(int64_t BH, int64_t d, int64_t m, int64_t b, int T, bool lens)
+// those of the half-steps).  Times against the half-steps':
+// - one step of few large heads, which two launches spread over m and b
+//   workgroups a head: at 128 columns, 4 heads: 16 x 16 rows 1.19 (8.5 us),
+//   15 x 14 1.11, 16 x 4 0.99, 8 x 8 0.94, with lengths 1.22, 1.16, 1.03, 1.00;
+//   24 heads of 16 x 16 1.01, 32 heads 0.95.  At 96 columns 16 x 16 rows 1.06
+//   for 4 heads, 1.01 for 12, 0.94 for 24; smaller heads 0.85 to 0.99;
+// - one step of many tiny heads (d = 72; at 128 columns up to 0.1 more): 512
+//   heads of 2, 6 and 9 units 1.11, 0.98 and 0.90, but 290 to 320 heads of 9
+//   units 1.06 to 1.11; 1024 heads of 8, 10 and 12 units 1.10, 1.02 and 0.87;
+//   4096 heads of 12, 16 and 17 units 1.21, 0.88 and 0.95 to 1.08;
+// - two steps: 0.3 to 0.7 up to 512 heads; 1024 heads of 3, 6 and 8 units 1.16,
+//   0.91 and 0.76; 4096 heads of 8, 10, 12 and 17 units 1.17, 1.05, 0.90, 0.76.
+//   Three steps: 1024 heads of 3 and 5 units 0.97 and 0.83; 4096 heads of 6, 8
+//   and 9 units 1.17, 1.00 and 0.95.
+inline bool one_launch_forward(int64_t BH, int64_t d, int64_t m, int64_t b, int T, bool lens, int64_t num_cus)
 {
     const bool wide = tile_d(d) == 128;
     const int64_t rows = wide ? (lens ? 64 : 144) : 256;
-    return T > 1 || m * b < rows || BH >= (wide ? 24 : 12);
+    if (T == 1 && m * b >= rows && BH < (wide ? 24 : 12)) return false;
+    return T == 1 ? fills_rounds(BH, m + b, num_cus, 1, 8, 4) : fills_rounds(BH, m + b, num_cus, 2, T == 2 ? 6 : 4, 1);
 }
 
 // The same for the gradient's recompute, at any d.  One step is one launch on
 // the half-steps too, of m workgroups a head: the whole gradient takes 1.0 to
 // 1.4 times as long with one (4 to 256 heads; 1.0 to 1.17 from 384 to 2048).
-// Two steps are three launches: 0.90 to 1.0 of them, but 1.0 to 1.16 at 128
-// columns below 64 heads; three steps 0.85 to 1.06 of five.
-inline bool one_launch_recompute(int64_t BH, int64_t d, int T)
+// Two steps are three launches: 0.85 to 1.0 of the gradient up to 256 heads, but
+// - few large heads (1 to 63): at 128 columns 16 x 16 rows 1.02 to 1.10, 15 x 14
+//   1.02 to 1.09, 16 x 8 0.99 to 1.04, 16 x 4 0.96 to 1.01, 8 x 8 0.97; at 96
+//   columns 16 x 16 rows 1.03 to 1.05, 15 x 14 0.98 (100 heads: 0.98 at most);
+// - many tiny heads: 512 heads of 2, 8 and 10 units 0.97 to 1.09, 0.98 to 1.02
+//   and 0.97 to 1.02; 1024 heads of 6, 10 and 12 units 1.07 to 1.14, 1.05 and
+//   1.00 to 1.02; 4096 heads of 2, 12, 16 and 18 units 1.7, 1.05, 1.00 and 1.02.
+// Three steps: up to 512 heads 0.82 to 1.03; 1024 heads of 6 and 8 units 1.01 to
+// 1.06 and 0.98 to 1.02; 4096 heads of 10, 12 and 16 units 1.05, 1.02 and 0.97.
+inline bool one_launch_recompute(int64_t BH, int64_t d, int64_t m, int64_t b, int T, int64_t num_cus)
 {
-    return T > 2 || (T == 2 && (tile_d(d) < 128 || BH >= 64));
+    const int D = tile_d(d);
+    if (T == 1 || (T == 2 && BH < 64 && D > 64 && m * b >= (D == 128 ? 128 : 256))) return false;
+    return T == 2 ? fills_rounds(BH, m + b, num_cus, 1, 6, 8) : fills_rounds(BH, m + b, num_cus, 2, 4, 4);
 }
 
 // The family that runs a call under `path` (kFamNone: the forced path does

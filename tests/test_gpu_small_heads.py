@@ -104,28 +104,36 @@ def test_gradient_recompute_gives_the_bits_of_the_half_steps(ma, dtype, B, H, n,
     (1, 11, 16, 16, 96, 1, False, False), (1, 12, 16, 16, 72, 1, True, False), (1, 4, 15, 14, 96, 1, True, False),
     (1, 4, 8, 8, 128, 1, True, False), (3, 300, 16, 16, 64, 1, True, False), (1, 2, 16, 16, 64, 2, True, True),
     (1, 63, 16, 16, 128, 2, True, False), (2, 32, 16, 16, 128, 2, True, True), (1, 2, 4, 16, 96, 2, True, True),
-    (1, 1, 16, 16, 128, 3, True, True),
+    (1, 1, 16, 16, 128, 3, True, True), (1, 63, 8, 15, 128, 2, True, True), (1, 63, 8, 16, 104, 2, True, False),
+    (1, 4, 16, 16, 96, 2, True, False), (1, 4, 16, 15, 72, 2, True, True),
+    # many tiny heads (256 compute units)
+    (1, 256, 1, 1, 72, 1, True, False), (1, 257, 4, 5, 72, 1, False, False), (1, 512, 4, 6, 72, 1, True, False),
+    (1, 1025, 4, 8, 128, 1, False, False), (2, 2000, 8, 8, 128, 1, True, False), (1, 1024, 2, 5, 104, 2, True, False),
+    (1, 1025, 2, 5, 104, 2, False, False), (1, 512, 1, 1, 72, 2, True, False), (1, 1028, 1, 4, 72, 3, False, False),
+    (4, 900, 2, 5, 72, 3, False, False), (4, 1000, 4, 4, 72, 3, True, False), (1, 512, 4, 6, 64, 2, True, True),
+    (1, 513, 4, 6, 64, 2, True, False), (2, 1500, 8, 8, 96, 2, True, True), (1, 512, 1, 1, 96, 3, True, True),
+    (1, 1025, 4, 4, 96, 3, True, False), (1, 256, 1, 1, 64, 2, True, True),
 ])
 def test_one_launch_where_it_is_faster(ma, B, H, m, b, d, T, forward, recompute):
-    """The lines of the automatic path: one step of few large heads, and the
-    recompute of one step, run on the half-steps."""
+    """The lines of the automatic path: one step of few large heads, many tiny
+    heads, and the recompute of one step, run on the half-steps."""
     import torch
 
+    half = ["r_half_step", "l_half_step"] * (T - 1) + ["r_half_step_final"]
     q, k, v, g = (torch.randn(B, H, m * b, d, device="cuda", dtype=torch.bfloat16) for _ in range(4))
     out, grads = torch.empty_like(q), [torch.empty_like(q) for _ in range(3)]
     ma.monarch_attn_timing_enable(True)
     try:
         ma.monarch_attn_fwd(q, k, v, out, m, b, T)
         assert [kind for kind, _ in ma.monarch_attn_timing_read()] == (
-            ["monarch_fused_head"] if forward else ["r_half_step_final", "monarch_apply"])
+            ["monarch_fused_head"] if forward else half + ["monarch_apply"])
         lens = torch.full((B,), m * b, device="cuda", dtype=torch.int32)
         ma.monarch_attn_fwd_varlen(q, k, v, out, lens, m, b, T)
         few = T == 1 and d > 96 and m * b >= 64 and B * H < 24  # with lengths, heads of 64 rows up
         assert [kind for kind, _ in ma.monarch_attn_timing_read()] == (
-            ["monarch_fused_head"] if forward and not few else ["r_half_step_final", "monarch_apply"])
+            ["monarch_fused_head"] if forward and not few else half + ["monarch_apply"])
         ma.monarch_attn_bwd(q, k, v, g, *grads, m, b, T)
         kinds = [kind for kind, _ in ma.monarch_attn_timing_read()]
-        half = ["r_half_step", "l_half_step"] * (T - 1) + ["r_half_step_final"]
         assert kinds == (["monarch_fused_head"] if recompute else half) + ["l_bwd", "r_bwd"] * T
     finally:
         ma.monarch_attn_timing_enable(False)
