@@ -33,10 +33,10 @@ inline dim3 unit_grid(const void *kern, int threads, int64_t units, int num_cus)
 template <typename T, int NB, int D, bool FIRST, bool FINAL, bool RG, bool LENS>
 int launch_r1(Launcher &L, const CallBufs &B, ma::HeadDims hd, int64_t BH, int num_cus)
 {
-    constexpr int W = ma::Split<NB / 16>::W;
+    constexpr int NTH = ma::RUnit<T, NB, D, FIRST, FINAL, RG, LENS>::NTH;
     auto kern = ma::r_half_step<T, NB, D, FIRST, FINAL, RG, LENS>;
     hd.units = BH * hd.m;
-    const dim3 grid = unit_grid((const void *)kern, 64 * W, hd.units, num_cus), block(64 * W);
+    const dim3 grid = unit_grid((const void *)kern, NTH, hd.units, num_cus), block(NTH);
     const ma::Bufs<T> p = typed<T>(B);
     return L.run(FINAL ? kRFinal : kR,
                  [&] { return launched([&] { hipLaunchKernelGGL(kern, grid, block, 0, L.stream, p, hd); }); });
@@ -54,17 +54,18 @@ int launch_r(Launcher &L, const CallBufs &B, ma::HeadDims hd, int64_t BH, int nu
 template <typename T, int NM, int D, bool RG, bool LENS = false>
 int launch_l(Launcher &L, const CallBufs &B, ma::HeadDims hd, int64_t BH, int num_cus, bool apply)
 {
-    constexpr int W = ma::Split<NM / 16>::W;
+    constexpr int NTH = ma::LUnit<T, NM, D, RG, LENS>::NTH;
+    static_assert(NTH == ma::ApplyUnit<T, NM, D, RG, LENS>::NTH, "one workgroup size for both L units");
     hd.units = BH * hd.b;
     const ma::Bufs<T> p = typed<T>(B);
-    const dim3 block(64 * W);
+    const dim3 block(NTH);
     if (apply) {
         auto kern = ma::monarch_apply<T, NM, D, RG, LENS>;
-        const dim3 grid = unit_grid((const void *)kern, 64 * W, hd.units, num_cus);
+        const dim3 grid = unit_grid((const void *)kern, NTH, hd.units, num_cus);
         return L.run(kApply, [&] { return launched([&] { hipLaunchKernelGGL(kern, grid, block, 0, L.stream, p, hd); }); });
     }
     auto kern = ma::l_half_step<T, NM, D, RG, LENS>;
-    const dim3 grid = unit_grid((const void *)kern, 64 * W, hd.units, num_cus);
+    const dim3 grid = unit_grid((const void *)kern, NTH, hd.units, num_cus);
     return L.run(kL, [&] { return launched([&] { hipLaunchKernelGGL(kern, grid, block, 0, L.stream, p, hd); }); });
 }
 

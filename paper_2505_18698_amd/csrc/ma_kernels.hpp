@@ -576,29 +576,37 @@ template <typename U, int D, typename T> __device__ inline void run_units(const 
         run_units_d<U, 0, true>(p, hd, per, lds);
 }
 
+// The unit that a launch runs, whose NTH threads are its workgroup.
 template <typename T, int NB, int D, bool FIRST, bool FINAL, bool RAGGED, bool LENS>
-__global__ __launch_bounds__(64 * Split<NB / 16>::W) void r_half_step(Bufs<T> p, HeadDims hd)
-{
-    using U = typename std::conditional<std::is_same<T, float>::value, RHalf32<NB, D, FIRST, FINAL, RAGGED, LENS>,
+using RUnit = typename std::conditional<std::is_same<T, float>::value, RHalf32<NB, D, FIRST, FINAL, RAGGED, LENS>,
                                         RHalf<T, NB, D, FIRST, FINAL, RAGGED, LENS>>::type;
+template <typename T, int NM, int D, bool RAGGED, bool LENS>
+using LUnit = typename std::conditional<std::is_same<T, float>::value, LHalf32<NM, D, RAGGED, LENS>,
+                                        LHalf<T, NM, D, RAGGED, LENS>>::type;
+template <typename T, int NM, int D, bool RAGGED, bool LENS>
+using ApplyUnit = typename std::conditional<std::is_same<T, float>::value, Apply32<NM, D, RAGGED, LENS>,
+                                            Apply<T, NM, D, RAGGED, LENS>>::type;
+
+template <typename T, int NB, int D, bool FIRST, bool FINAL, bool RAGGED, bool LENS>
+__global__ __launch_bounds__((RUnit<T, NB, D, FIRST, FINAL, RAGGED, LENS>::NTH)) void r_half_step(Bufs<T> p, HeadDims hd)
+{
+    using U = RUnit<T, NB, D, FIRST, FINAL, RAGGED, LENS>;
     __shared__ __attribute__((aligned(16))) char lds[U::LDS_BYTES];
     run_units<U, D>(p, hd, hd.m, lds);
 }
 
 template <typename T, int NM, int D, bool RAGGED, bool LENS>
-__global__ __launch_bounds__(64 * Split<NM / 16>::W) void l_half_step(Bufs<T> p, HeadDims hd)
+__global__ __launch_bounds__((LUnit<T, NM, D, RAGGED, LENS>::NTH)) void l_half_step(Bufs<T> p, HeadDims hd)
 {
-    using U = typename std::conditional<std::is_same<T, float>::value, LHalf32<NM, D, RAGGED, LENS>,
-                                        LHalf<T, NM, D, RAGGED, LENS>>::type;
+    using U = LUnit<T, NM, D, RAGGED, LENS>;
     __shared__ __attribute__((aligned(16))) char lds[U::LDS_BYTES];
     run_units<U, D>(p, hd, hd.b, lds);
 }
 
 template <typename T, int NM, int D, bool RAGGED, bool LENS>
-__global__ __launch_bounds__(64 * Split<NM / 16>::W) void monarch_apply(Bufs<T> p, HeadDims hd)
+__global__ __launch_bounds__((ApplyUnit<T, NM, D, RAGGED, LENS>::NTH)) void monarch_apply(Bufs<T> p, HeadDims hd)
 {
-    using U = typename std::conditional<std::is_same<T, float>::value, Apply32<NM, D, RAGGED, LENS>,
-                                        Apply<T, NM, D, RAGGED, LENS>>::type;
+    using U = ApplyUnit<T, NM, D, RAGGED, LENS>;
     __shared__ __attribute__((aligned(16))) char lds[U::LDS_BYTES];
     run_units<U, D>(p, hd, hd.b, lds);
 }

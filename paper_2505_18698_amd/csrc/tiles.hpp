@@ -369,9 +369,9 @@ __device__ inline f32x4 gemm_colsum(const ProbFrags<T, NT> &pf)
     return acc;
 }
 
-// Row tiles per wave and waves per workgroup for a block of NT 16-row tiles:
-// two tiles per wave from 4 tiles up, so that every operand fragment read
-// from LDS feeds two MFMAs.
+// Row tiles per wave and waves per workgroup of a 16-bit unit of NT 16-row
+// tiles: one tile a wave.  MA_ROW_TILES = 2 gives a wave two from 4 tiles up, so
+// that every operand fragment read from LDS feeds two MFMAs.
 #ifndef MA_ROW_TILES
 #define MA_ROW_TILES 1
 #endif
