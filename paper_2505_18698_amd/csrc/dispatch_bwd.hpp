@@ -34,8 +34,7 @@ int launch_r_bwd(Launcher &L, const ma::BwdBufs<T> &p, const ma::BwdDims &dm, in
 
 // One launch of the L-update gradient of a step, on tiles of S >= m rows (and
 // of the R-update gradient, S >= b): each kernel takes the tile of its own
-// dimension.  128-row tiles at D = 128 hold 16-bit unit tiles (16-bit
-// elements only, the only ones the forward takes at that size).
+// dimension.
 template <typename T, int D, bool LENS>
 int l_bwd_step(Launcher &L, const ma::BwdBufs<T> &p, const ma::BwdDims &dm, int64_t BH, bool last)
 {

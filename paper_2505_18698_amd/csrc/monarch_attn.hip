@@ -330,9 +330,7 @@ int forward(const void *q, const void *k, const void *v, void *out, float *obj, 
 
 // ---- gradient ----
 
-// The gradient takes every shape the forward takes (its 128-row units at
-// D = 128 hold the tiles that are exact in the 16-bit element type as such),
-// for T <= 32.
+// The gradient takes every shape the forward takes, for T <= 32.
 int check_bwd_shape(int64_t N, int64_t d, int64_t m, int64_t b, int32_t T, int32_t dtype)
 {
     const int rc = check_shape(N, d, m, b, T, dtype);
