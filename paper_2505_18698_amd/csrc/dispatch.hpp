@@ -322,7 +322,7 @@ template <typename T> int run_call_impl(Launcher &L, const CallBufs &B, const Ca
 // The forward half-steps again, each step's states to buffers of their own,
 // then the reverse sweep.  States with rows of d elements; every (m, b, d) the
 // forward takes.
-template <typename T, int D> int run_bwd_d(Launcher &L, const BwdCallBufs &B, const CallDims &c, int path)
+template <typename T, int D> int run_bwd_d(Launcher &L, const BwdCallBufs &B, const CallDims &c)
 {
     ma::HeadDims hd{c.m, c.b, c.n, c.d, c.s_log2e, 0};
     hd.T = c.T;
@@ -332,7 +332,7 @@ template <typename T, int D> int run_bwd_d(Launcher &L, const BwdCallBufs &B, co
     if constexpr (sizeof(T) == 2) {
         // small heads: one launch of the one-workgroup-per-head kernel, the
         // states to memory as it goes
-        if (path == kAuto && small_heads(MA_BF16, c.m, c.b) && one_launch_recompute(c.BH, c.d, c.m, c.b, c.T, c.num_cus)) {
+        if (B.path == kAuto && small_heads(MA_BF16, c.m, c.b) && one_launch_recompute(c.BH, c.d, c.m, c.b, c.T, c.num_cus)) {
             const CallBufs f{B.q, B.k, B.v, nullptr, B.aR, B.aL, B.Y, B.cR, B.cL, nullptr, nullptr, B.lens};
             if ((rc = run_fused_states<T>(L, f, hd, c, (int64_t)(B.st / sizeof(T)), (int64_t)B.cst)) != MA_OK) return rc;
             return bwd_sweep<T, D>(L, B, c);
@@ -354,12 +354,12 @@ template <typename T, int D> int run_bwd_d(Launcher &L, const BwdCallBufs &B, co
     return bwd_sweep<T, D>(L, B, c);
 }
 
-template <typename T> int run_bwd_impl(Launcher &L, const BwdCallBufs &B, const CallDims &c, int path)
+template <typename T> int run_bwd_impl(Launcher &L, const BwdCallBufs &B, const CallDims &c)
 {
     switch (tile_d(c.d)) {
-    case 64: return run_bwd_d<T, 64>(L, B, c, path);
-    case 96: return run_bwd_d<T, 96>(L, B, c, path);
-    default: return run_bwd_d<T, 128>(L, B, c, path);
+    case 64: return run_bwd_d<T, 64>(L, B, c);
+    case 96: return run_bwd_d<T, 96>(L, B, c);
+    default: return run_bwd_d<T, 128>(L, B, c);
     }
 }
 

@@ -210,6 +210,7 @@ struct BwdCallBufs {
     size_t st, cst;
     float *dQ, *dK, *daL, *dcL, *dY, *daR, *dcR;
     const int *lens = nullptr;  // [B] real rows per batch element (device), or null
+    int path = kAuto;
 };
 
 // The gradient's reverse sweep for one element type and tile width (sweep_*.hip).
@@ -217,7 +218,7 @@ template <typename T, int D> int bwd_sweep(Launcher &L, const BwdCallBufs &B, co
 
 // Enqueue the gradient (forward recompute, then the reverse sweep) for one
 // element type; under a forced path the recompute runs the half-steps.
-template <typename T> int run_bwd(Launcher &L, const BwdCallBufs &B, const CallDims &c, int path);
+template <typename T> int run_bwd(Launcher &L, const BwdCallBufs &B, const CallDims &c);
 
 // Enqueue exact softmax attention (with the row logsumexps when lse != null).
 template <typename T> int run_exact(Launcher &L, const CallBufs &B, float *lse, int64_t BH, int n, int d);

@@ -404,6 +404,7 @@ int backward(const void *q, const void *k, const void *v, const void *dout, void
     BwdCallBufs bufs{};
     bufs.q = q, bufs.k = k, bufs.v = v, bufs.dout = dout, bufs.dq = dq, bufs.dk = dk, bufs.dv = dv;
     bufs.lens = lens;
+    bufs.path = g_path.load();
     char *p = base;
     bufs.st = lay.st;
     bufs.cst = lay.cs / sizeof(float);
@@ -427,9 +428,9 @@ int backward(const void *q, const void *k, const void *v, const void *dout, void
     if (!L.timed) tlock.unlock();
     (void)hipGetLastError();
     switch (dtype) {
-    case MA_F32: rc = run_bwd<float>(L, bufs, dims, g_path.load()); break;
-    case MA_BF16: rc = run_bwd<__bf16>(L, bufs, dims, g_path.load()); break;
-    default: rc = run_bwd<_Float16>(L, bufs, dims, g_path.load()); break;
+    case MA_F32: rc = run_bwd<float>(L, bufs, dims); break;
+    case MA_BF16: rc = run_bwd<__bf16>(L, bufs, dims); break;
+    default: rc = run_bwd<_Float16>(L, bufs, dims); break;
     }
     if (L.timed) {
         g_timing.nlaunch = L.n;
