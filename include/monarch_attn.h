@@ -267,9 +267,10 @@ int monarch_attn_exact_fwd(const void *q, const void *k, const void *v, void *ou
  *                 for bf16 and fp16 (else MA_EUNSUPPORTED).
  *
  * Runs the forward half-steps again, keeping the states of every step (one
- * launch for two and more steps of 16-bit heads with m, b <= 16), then one
- * launch per half-step in reverse order; all of it on `stream`, asynchronously.  The arithmetic of the reverse sweep is fp32 (the states
- * of the recomputed forward pass are in the element type, as in
+ * launch for two and more steps of 16-bit heads with m, b <= 16 where that is
+ * faster), then one launch per half-step in reverse order; all of it on
+ * `stream`, asynchronously.  The arithmetic of the reverse sweep is fp32 (the
+ * states of the recomputed forward pass are in the element type, as in
  * monarch_attn_fwd), and the result is deterministic (no atomics).
  * Workspace: monarch_attn_bwd_workspace_bytes(), in the same per-(device,
  * stream) buffer as monarch_attn_fwd (same rules).  Errors as
@@ -359,7 +360,8 @@ int monarch_attn_release_workspace(void);
  * Automatic selection takes path 2 where it applies; else path 3 where it
  * applies with m <= 32; else path 1, whose launches become the one kernel of
  * path 2 for 16-bit heads with m, b <= 16 and d > 64 where that is faster (not
- * for one step of a few large heads; path 1's workspace rules hold for them).  All paths compute the same operation with the same
+ * for one step of a few large heads, nor for many tiny ones; path 1's workspace
+ * rules hold for them).  All paths compute the same operation with the same
  * per-unit arithmetic, and give the same bits.
  */
 int monarch_attn_set_path(int32_t path);

@@ -50,10 +50,17 @@
 //
 // What bounds it: VALU issue and the latency of the phases between barriers.
 // At 16 heads of 128 x 128 blocks, d = 64, T = 2, bf16, the four launches take
-// r_bwd 201 and 126 us (t = 2, t = 1), l_bwd 147 and 168 us; on the fp32
+// r_bwd 194 and 120 us (t = 2, t = 1), l_bwd 145 and 160 us; on the fp32
 // matrix instruction, with the factors in LDS as fp32, they took 390, 347,
 // 289 and 345 us.  Their bytes alone (67 MB a state in fp32) take about 70 us
-// each.  VALU is active 40% of the time and the matrix cores 25%.
+// each.  VALU is active 35% of the time (46% in r_bwd at t = 1), the matrix cores
+// 23% in r_bwd, 13 and 17% in l_bwd.
+//
+// What it costs: with few units in flight a launch takes one unit's chain, which
+// is longer where one wave runs a unit of few rows that four ran.  Gradients
+// of fp32 and fp16 heads of up to 15 rows (fp32 at d > 96 above all) take 2 to
+// 15% longer than on the fp32 instruction (91 fp32 heads of 2 x 1 rows, d = 128,
+// T = 3: 64 -> 74 us, of which the six launches of the sweep 53 -> 60).
 //
 // The gradients of the states and the dQ, dK accumulators are fp32 in the
 // workspace.  Within a launch the units write disjoint rows, and launches that

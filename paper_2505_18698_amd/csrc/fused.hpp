@@ -23,8 +23,8 @@
 // store), not bytes or instructions, so heads should share a compute unit.
 // With Q, K and two state regions all in LDS (148 KB at D = 64) one head
 // filled it; two regions (76 KB) and 64 VGPRs a wave let two run side by side:
-// 384 heads of 15 x 14 rows, T = 2: 15.2 -> 13.8 us; 16 heads of 16 x 16
-// (one a compute unit either way): 7.9 -> 7.4 us.  Two blocks a wave (8 waves,
+// 384 heads of 15 x 14 rows (197 real), T = 2: 15.2 -> 13.7 us a call; 16 heads of
+// 16 x 16 (one a compute unit either way): 7.9 -> 7.1 us.  Two blocks a wave (8 waves,
 // 128 VGPRs) took 15.5 us on the first: a wave's phases double in length.
 // Wider tiles (109 and 142 KB) keep one head a compute unit; 512 heads of
 // 16 x 16 at d = 72, T = 3, take 27 us against 100 us on the half-steps, which
