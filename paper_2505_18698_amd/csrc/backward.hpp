@@ -56,11 +56,11 @@
 // each.  VALU is active 35% of the time (46% in r_bwd at t = 1), the matrix cores
 // 23% in r_bwd, 13 and 17% in l_bwd.
 //
-// What it costs: with few units in flight a launch takes one unit's chain, which
-// is longer where one wave runs a unit of few rows that four ran.  Gradients
-// of fp32 and fp16 heads of up to 15 rows (fp32 at d > 96 above all) take 2 to
-// 15% longer than on the fp32 instruction (91 fp32 heads of 2 x 1 rows, d = 128,
-// T = 3: 64 -> 74 us, of which the six launches of the sweep 53 -> 60).
+// What it costs: one wave runs a 16-row unit that four waves ran on the fp32
+// instruction, and where its rows are mostly padding its chain is longer.
+// Gradients of blocks of one to three rows take 2 to 6% longer in fp32 and fp16,
+// in fp32 at d > 96 up to 15% (91 heads of 2 x 1 rows, d = 128, T = 3: 64 -> 74 us;
+// 281 of 12 x 2, d = 104: 202 -> 227).
 //
 // The gradients of the states and the dQ, dK accumulators are fp32 in the
 // workspace.  Within a launch the units write disjoint rows, and launches that
